@@ -56,12 +56,30 @@ __device__ __forceinline__ bf16x8_t as_bf16x8(uint4 v) {
 // past the wave-uniform LDS address); the swizzle is its own inverse, so the
 // lane that fills position p of row r fetches chunk swz_chunk<BK>(r, p).
 // ---------------------------------------------------------------------------
-typedef __attribute__((address_space(3))) void lds_void_t;
-
 template <int BK>
 __device__ __forceinline__ int swz_chunk(int row, int chunk) {
   static_assert(BK == 64 || BK == 32, "chunk width");
   return BK == 64 ? (chunk ^ ((row >> 1) & 7)) : (chunk ^ ((row >> 2) & 3));
+}
+
+// A value that is the same in every lane, moved to an SGPR. Inline asm: the
+// compiler drops the builtin where it knows the value to be uniform, and then
+// keeps what is computed from it (an integer quotient comes from the vector
+// unit) in VGPRs, chunk addresses and loop bounds among them. The compiler
+// does not look into the asm for hazards, so it holds the wait states of both
+// sides: a vector instruction that wrote v just before, and a vector memory
+// instruction that uses the SGPR next.
+__device__ __forceinline__ int uniform_int(int v) {
+  int r;
+  asm volatile("s_nop 1\n\tv_readfirstlane_b32 %0, %1\n\ts_nop 4" : "=s"(r) : "v"(v));
+  return r;
+}
+
+// LDS byte address of a pointer into LDS: the low half of a generic address
+// in the shared aperture (a cast to the LDS address space would test the
+// pointer for null first, in scalar or vector code, at every use).
+__device__ __forceinline__ uint32_t lds_addr(const void* p) {
+  return __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(reinterpret_cast<uintptr_t>(p)));
 }
 
 // The load is issued through inline assembly, so the compiler does not track
@@ -72,8 +90,8 @@ __device__ __forceinline__ int swz_chunk(int row, int chunk) {
 // younger loads only make those waits more conservative. Nothing else in
 // these kernels uses M0.
 __device__ __forceinline__ void dma16(const void* gaddr, const bf16_t* lds) {
-  const uint32_t m0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_void_t*)lds));
-  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
+  const uint32_t m0 = lds_addr(lds);
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %0, off"
                :
                : "v"(gaddr), "s"(m0)
                : "memory");
@@ -90,17 +108,34 @@ __device__ __forceinline__ const void* uniform_ptr(const void* p) {
   return reinterpret_cast<const void*>((static_cast<uint64_t>(hi) << 32) | lo);
 }
 
-__device__ __forceinline__ void dma16s(const void* sbase, uint32_t voff, const void* lds) {
-  const uint32_t m0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_void_t*)lds));
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+// dma16s / dma4s to an LDS byte address (wave-uniform).
+__device__ __forceinline__ void dma16a(const void* sbase, uint32_t voff, uint32_t m0) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %0, %1"
+               :
+               : "v"(voff), "s"(sbase), "s"(m0)
+               : "memory");
+}
+// dma16a to LDS byte address m0 + off, off a constant after inlining.
+__device__ __forceinline__ void dma16o(const void* sbase, uint32_t voff, uint32_t m0, int off) {
+  asm volatile("s_add_u32 m0, %2, %3\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %0, %1"
+               :
+               : "v"(voff), "s"(sbase), "s"(m0), "is"(off)
+               : "memory", "scc");
+}
+__device__ __forceinline__ void dma4a(const void* sbase, uint32_t voff, uint32_t m0) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 3\n\tglobal_load_lds_dword %0, %1"
                :
                : "v"(voff), "s"(sbase), "s"(m0)
                : "memory");
 }
 
+__device__ __forceinline__ void dma16s(const void* sbase, uint32_t voff, const void* lds) {
+  dma16a(sbase, voff, lds_addr(lds));
+}
+
 __device__ __forceinline__ void dma4s(const void* sbase, uint32_t voff, const void* lds) {
-  const uint32_t m0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_void_t*)lds));
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1"
+  const uint32_t m0 = lds_addr(lds);
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 3\n\tglobal_load_lds_dword %0, %1"
                :
                : "v"(voff), "s"(sbase), "s"(m0)
                : "memory");
@@ -216,6 +251,11 @@ __device__ __forceinline__ void pipeline(int nK, bf16_t* smem, int stage_elems, 
 // program order (the issue order is still set by mix()). A consumer can then
 // refill an operand register right after its last MFMA of the k-step instead
 // of keeping a second buffer for it.
+//
+// The loads of a chunk leave in KS parts, issue(kc, live, stage, part), one
+// per k-step from the one after the barrier on: a burst of all of them fills
+// the CU's miss queue, and the wave then sits in the issue of the rest while
+// its MFMAs wait behind them. part < 0 asks for all parts at once (prologue).
 template <int NS, int LOADS, int KS, bool MMA_FIRST = false, class Issue, class Read, class Mma, class Mix>
 __device__ __forceinline__ void pipeline_xk(int nK, bf16_t* smem, int stage_elems, Issue&& issue, Read&& read,
                                             Mma&& mma, Mix&& mix) {
@@ -223,18 +263,21 @@ __device__ __forceinline__ void pipeline_xk(int nK, bf16_t* smem, int stage_elem
   static_assert(KS >= 2 && KS % 2 == 0, "k-steps per chunk");
   wait_vmcnt<0>();  // nothing older (e.g. a previous tile's stores) is left in the count
 #pragma unroll
-  for (int i = 0; i < NS - 1; ++i) issue(i, i < nK, smem + i * stage_elems);
+  for (int i = 0; i < NS - 1; ++i) issue(i, i < nK, smem + i * stage_elems, -1);
   wait_vmcnt<LOADS * (NS - 2)>();  // chunk 0 landed
   lds_barrier();
-  issue(NS - 1, NS - 1 < nK, smem + (NS - 1) * stage_elems);  // stage NS-1 holds nothing yet
+  issue(NS - 1, NS - 1 < nK, smem + (NS - 1) * stage_elems, 0);  // stage NS-1 holds nothing yet
   read(smem, 0, 0);
   int cur = 0;
   for (int c = 0; c < nK; ++c) {
     const bf16_t* st = smem + cur * stage_elems;
     const int nxt = (cur + 1 == NS) ? 0 : cur + 1;
+    bf16_t* prev = smem + (cur == 0 ? NS - 1 : cur - 1) * stage_elems;  // being refilled with chunk c+NS-1
+    const bool live = c + NS - 1 < nK;
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int s = 0; s + 1 < KS; ++s) {
+      issue(c + NS - 1, live, prev, s + 1);
       if (MMA_FIRST) {
         mma(s & 1);
         read(st, s + 1, (s + 1) & 1);
@@ -249,7 +292,7 @@ __device__ __forceinline__ void pipeline_xk(int nK, bf16_t* smem, int stage_elem
     wait_lgkmcnt0();                 // this wave's reads of chunk c returned
     wait_vmcnt<LOADS * (NS - 2)>();  // chunk c+1 landed
     lds_barrier();                   // every wave: chunk c+1 landed, chunk c read
-    issue(c + NS, c + NS < nK, smem + cur * stage_elems);
+    issue(c + NS, c + NS < nK, smem + cur * stage_elems, 0);
     __builtin_amdgcn_sched_barrier(0);
     // first fragments of chunk c+1 (after the last chunk: an unused read of a
     // stage that holds a placeholder load; LDS reads cannot fault)

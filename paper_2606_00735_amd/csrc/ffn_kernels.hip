@@ -25,30 +25,33 @@ namespace moe {
 
 constexpr int kBK = 64;  // K chunk per pipeline stage (128-byte tile rows)
 
-// Blocks of 8 waves (two per SIMD, so one wave's LDS waits are covered by
-// the other's MFMAs). Tile classes (see row_tiles):
-//   small   64 x 128 tiles, waves 2x4   (weight streaming at small M_e)
-//   mid    128 x 128 tiles, waves 2x4
-//   large  256 x 128 tiles, waves 4x2   (MFMA bound)
+// Tile classes (see row_tiles):
+//   small   64 x 128 tiles   (weight streaming at small M_e)
+//   mid    128 x 128 tiles
+//   large  256 x 128 tiles   (MFMA bound; see big_tile)
 // with 128 output columns per matrix (gate and up both, in the dual GEMM).
 // K advances in 64-wide chunks (whole 128-byte cache lines per tile row);
-// each class keeps as many chunks in flight as 144 KB of LDS allows
+// small and mid tiles keep as many chunks in flight as 144 KB of LDS allows
 // (Stages below).
-constexpr int kWaves = 8;
-constexpr int kThreads = kWaves * kWave;
+//
+// Blocks have W waves. W = 4, one wave per SIMD with the whole register file,
+// is what the large tile needs. W = 8 serves launches in which no expert can
+// have more than 128 rows: the small and mid tiles run 2-7 % faster with a
+// second wave per SIMD covering the first one's LDS waits and epilogue.
+constexpr int kMaxWaves = 8;
 constexpr int kSmallM = 64;
-constexpr int kDmaRows = kWaves * 1024 / (2 * kBK);  // rows one DMA round of all waves covers
 
-template <int BM, int BN, bool DUAL>
+template <int BM, int BN, bool DUAL, int W>
 struct Stages {
   static constexpr int NB = DUAL ? 2 : 1;
-  static constexpr int AROWS = BM > kDmaRows ? BM : kDmaRows;  // A rows loaded per stage
+  static constexpr int DROWS = W * 1024 / (2 * kBK);       // rows one DMA round of all waves covers
+  static constexpr int AROWS = BM > DROWS ? BM : DROWS;    // A rows loaded per stage
   static constexpr int ROWS = AROWS + NB * BN;
   static constexpr int ELEMS = ROWS * kBK;
   static constexpr int FIT = (144 * 1024) / (ELEMS * 2);  // stages that fit in 144 KB of LDS
   static constexpr int NS = FIT < 2 ? 2 : (FIT > 8 ? 8 : FIT);
   static constexpr int BYTES = ELEMS * 2 * NS;
-  static constexpr int LOADS = ROWS / kDmaRows;  // DMA instructions per wave per chunk
+  static constexpr int LOADS = ROWS / DROWS;  // DMA instructions per wave per chunk
 };
 
 struct GemmArgs {
@@ -187,23 +190,79 @@ __device__ __forceinline__ void split_epilogue(const f32x16_t (&acc)[NB][MI][NI]
   if (COH) wait_vmcnt<0>();
 }
 
+// A wave's ROWS x COLS block of a tile's output, from the MFMA register layout
+// to memory in whole rows. There a lane holds 4 consecutive columns of a row
+// per register group (for each 32 x 32 block (i, j): row 32 i + lane % 32,
+// columns 32 j + 8 g + 4 (lane / 32), g = 0..3), so direct stores write 8 (or,
+// MXFP8 codes, 4) bytes to each of 32 rows at once, 16 (8) bytes of a cache
+// line at a time, and the line requests of 64 such stores cost a 256 x 256
+// tile several microseconds. Through a piece of LDS of its own (free after the
+// K loop) the wave stores 16 bytes a lane and whole 64- to 256-byte rows.
+// put(i, j, g) returns the group's 4 columns (EB bytes each); rows at or past
+// m_end are not stored. Ends with a barrier: the LDS is free again.
+template <int ROWS, int COLS, int EB, class Put>
+__device__ __forceinline__ void store_block(bf16_t* smem, void* C, int N, int row0, int m_end, int col0, int wave,
+                                            int lane, Put&& put) {
+  constexpr int RB = COLS * EB, PP = RB / 16;  // bytes and 16-byte pieces of a row
+  static_assert(RB == 256 || RB == 128 || RB == 64 || RB == 32, "row bytes");
+  // piece p of row r sits at p ^ key(r): 16 consecutive rows touch all banks
+  auto key = [](int r) {
+    return PP == 16 ? (r & 15) : PP == 8 ? ((r >> 1) & 7) : PP == 4 ? ((r >> 2) & 3) : ((r >> 3) & 1);
+  };
+  char* lds = reinterpret_cast<char*>(smem) + wave * (ROWS * RB);
+  // opaque: the addresses below are computed here and not kept in registers
+  // through the K loops
+  asm volatile("" : "+v"(lane));
+  const int r32 = lane & 31, hi = lane >> 5;
+  // 32 rows at a time, in a fixed order: the register budget has no room for more
+#pragma unroll
+  for (int i = 0; i < ROWS / 32; ++i) {
+    char* blk = lds + i * 32 * RB;
+#pragma unroll
+    for (int j = 0; j < COLS / 32; ++j)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const int byte = (j * 32 + 8 * g) * EB;  // of hi = 0; hi = 1: 4 EB further
+        char* q = blk + r32 * RB + (((byte / 16) ^ key(r32)) * 16) + byte % 16 + hi * 4 * EB;
+        if constexpr (EB == 2)
+          *reinterpret_cast<uint2*>(q) = put(i, j, g);
+        else
+          *reinterpret_cast<uint32_t*>(q) = put(i, j, g);
+      }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int it = 0; it < 32 * PP / 64; ++it) {
+      const int row = (it * 64 + lane) / PP, p = lane % PP;
+      const uint4 v = *reinterpret_cast<const uint4*>(blk + row * RB + ((p ^ key(row)) * 16));
+      const int out = row0 + i * 32 + row;
+      if (out < m_end)
+        *reinterpret_cast<uint4*>(reinterpret_cast<char*>(C) + ((size_t)out * N + col0) * EB + p * 16) = v;
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  wait_lgkmcnt0();
+  lds_barrier();
+}
+
 // One BM x BN output tile (two of them, gate and up, when DUAL) over the whole
-// K range: 8 waves, 32x32x16 bf16 MFMA, operands loaded straight from global
+// K range: W waves, 32x32x16 bf16 MFMA, operands loaded straight from global
 // memory into NS swizzled LDS stages (see pipeline_xk).
 // SPLIT: only K chunks [kc0, kc1) are summed and the fp32 sums of output
 // (r, c) (r: row within the tile, c: column within the tile) go to
 // pbase[b * pstride + r * pld + pcol0 + c] instead of C.
-template <int BM, int BN, int WAVES_M, bool DUAL, bool SPLIT = false, bool COH = false>
+template <int W, int BM, int BN, int WAVES_M, bool DUAL, bool SPLIT = false, bool COH = false>
 __device__ __forceinline__ void gemm_tile(const GemmArgs& a, bf16_t* smem, int e, int m0, int m_end, int n0,
                                           int kc0 = 0, int kc1 = -1, float* pbase = nullptr,
                                           size_t pstride = 0, int pld = 0, int pcol0 = 0, bool coh = true) {
-  using St = Stages<BM, BN, DUAL>;
+  using St = Stages<BM, BN, DUAL, W>;
   constexpr int NB = DUAL ? 2 : 1;
-  constexpr int WAVES_N = kWaves / WAVES_M;
+  constexpr int WAVES_N = W / WAVES_M;
   constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
   constexpr int MI = WM / 32, NI = WN / 32;
   constexpr int AR = St::AROWS;
   static_assert(MI >= 1 && NI >= 1, "wave tile");
+  e = uniform_int(e), m0 = uniform_int(m0), m_end = uniform_int(m_end), n0 = uniform_int(n0);
+  kc0 = uniform_int(kc0), kc1 = uniform_int(kc1);
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WAVES_N, wn = wave % WAVES_N;
@@ -225,39 +284,46 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, bf16_t* smem, int e
 
   // Loop-invariant byte offsets of this lane's 16-byte pieces (dma16s; the
   // chunk's column goes into the wave-uniform base): instruction t of wave w
-  // moves rows [8 (t kWaves + w), +8), lane l row l / 8, piece l % 8 of the
+  // moves rows [8 (t W + w), +8), lane l row l / 8, piece l % 8 of the
   // swizzled row; A rows past the tile re-read its last row. Both weight
   // matrices share offsets. A placeholder load (live == false) reads the
   // first 16 bytes of the chunk in every lane.
-  constexpr int RPI = 8, LA = AR / (RPI * kWaves), LB = BN / (RPI * kWaves);
-  static_assert(AR % (RPI * kWaves) == 0 && BN % (RPI * kWaves) == 0, "rows per wave");
+  constexpr int RPI = 8, LA = AR / (RPI * W), LB = BN / (RPI * W);
+  static_assert(AR % (RPI * W) == 0 && BN % (RPI * W) == 0, "rows per wave");
   uint32_t offA[LA], offB[LB];
 #pragma unroll
   for (int t = 0; t < LA; ++t) {
-    const int r = (t * kWaves + wave) * RPI + lane / 8;
+    const int r = (t * W + wave) * RPI + lane / 8;
     int rr = r < a_rows ? r : a_rows - 1;
     if (gather) rr = min(max(a.a_src[m0 + rr] / a.a_div, 0), a.a_T - 1);
     offA[t] = (uint32_t)rr * (uint32_t)(K * 2) + (uint32_t)(swz_chunk<kBK>(r, lane % 8) * 16);
   }
 #pragma unroll
   for (int t = 0; t < LB; ++t) {
-    const int r = (t * kWaves + wave) * RPI + lane / 8;
+    const int r = (t * W + wave) * RPI + lane / 8;
     offB[t] = (uint32_t)(r * LDB * 2 + swz_chunk<kBK>(r, lane % 8) * 16);
   }
   if (kc1 < 0) kc1 = K / kBK;
-  auto issue = [&](int kc, bool live, bf16_t* st) {
-    const size_t col = (size_t)(live ? kc0 + kc : kc0) * kBK;
-    const void* pa = uniform_ptr(A + col);
+  // part: the share of the chunk's loads to issue (pipeline_xk); < 0: all.
+  // With two stages all leave at once: the last would have no time to land.
+  constexpr int KS = kBK / 16;
+  auto issue = [&](int kc, bool live, bf16_t* st, int part) {
+    const int msk = live ? -1 : 0;
+    const size_t col = (size_t)(kc0 + (kc & msk)) * kBK;
+    const uint32_t l0 = lds_addr(st) + wave * (RPI * kBK * 2);
+    constexpr int LS = W * RPI * kBK * 2;  // LDS bytes between a wave's loads
+    auto mine = [&](int t) { return part < 0 || (St::NS > 2 ? t * KS / St::LOADS : 0) == part; };
 #pragma unroll
-    for (int t = 0; t < LA; ++t) dma16s(pa, live ? offA[t] : 0u, st + (t * kWaves + wave) * RPI * kBK);
-    const void* pb0 = uniform_ptr(B0 + col);
+    for (int t = 0; t < LA; ++t)
+      if (mine(t)) dma16a(uniform_ptr(A + col), offA[t] & (uint32_t)msk, l0 + t * LS);
 #pragma unroll
-    for (int t = 0; t < LB; ++t) dma16s(pb0, live ? offB[t] : 0u, st + (AR + (t * kWaves + wave) * RPI) * kBK);
+    for (int t = 0; t < LB; ++t)
+      if (mine(LA + t)) dma16a(uniform_ptr(B0 + col), offB[t] & (uint32_t)msk, l0 + AR * kBK * 2 + t * LS);
     if (DUAL) {
-      const void* pb1 = uniform_ptr(B1 + col);
 #pragma unroll
       for (int t = 0; t < LB; ++t)
-        dma16s(pb1, live ? offB[t] : 0u, st + (AR + BN + (t * kWaves + wave) * RPI) * kBK);
+        if (mine(LA + LB + t))
+          dma16a(uniform_ptr(B1 + col), offB[t] & (uint32_t)msk, l0 + (AR + BN) * kBK * 2 + t * LS);
     }
   };
   // Operands of k-step s+1 are read from LDS while the MFMAs of k-step s
@@ -294,7 +360,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, bf16_t* smem, int e
     if (NMFMA > PAIRS) __builtin_amdgcn_sched_group_barrier(0x008, NMFMA - PAIRS, 0);
     if (NREAD > PAIRS) __builtin_amdgcn_sched_group_barrier(0x100, NREAD - PAIRS, 0);
   };
-  pipeline_xk<St::NS, St::LOADS, kBK / 16>(kc1 - kc0, smem, St::ELEMS, issue, read, mma, mix);
+  pipeline_xk<St::NS, St::LOADS, KS>(kc1 - kc0, smem, St::ELEMS, issue, read, mma, mix);
 
   // Epilogue. The MFMAs computed transposed 32x32 blocks (weights as the A
   // operand): register v of lane l holds output column 8 * (v / 4) +
@@ -305,50 +371,73 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, bf16_t* smem, int e
     split_epilogue<MI, NI, NB, WM, WN, COH>(acc, m0, m_end, pcol0, pld, wm, wn, lane, pbase, pstride, coh);
     return;
   }
+  store_block<WM, WN, 2>(smem, a.C, N, m0 + wm * WM, m_end, n0 + wn * WN, wave, lane, [&](int i, int j, int g) {
+    float r[4];
 #pragma unroll
-  for (int i = 0; i < MI; ++i) {
-    const int row = m0 + wm * WM + i * 32 + (lane & 31);
-    if (row < m_end) {
-      bf16_t* crow = a.C + (size_t)row * N + n0 + wn * WN + 4 * (lane >> 5);
-#pragma unroll
-      for (int j = 0; j < NI; ++j)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          float r[4];
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const int v = 4 * g + q;
-            r[q] = DUAL ? silu_mul_fast(acc[0][i][j][v], acc[NB - 1][i][j][v]) : acc[0][i][j][v];
-          }
-          uint2 packed;
-          packed.x = pack_bf16x2(r[0], r[1]);
-          packed.y = pack_bf16x2(r[2], r[3]);
-          *reinterpret_cast<uint2*>(crow + j * 32 + 8 * g) = packed;
-        }
+    for (int q = 0; q < 4; ++q) {
+      const int v = 4 * g + q;
+      r[q] = DUAL ? silu_mul_fast(acc[0][i][j][v], acc[NB - 1][i][j][v]) : acc[0][i][j][v];
     }
-  }
+    return make_uint2(pack_bf16x2(r[0], r[1]), pack_bf16x2(r[2], r[3]));
+  });
 }
 
 // MXFP8 stages: the same 128-byte tile rows as the bf16 path (a K chunk is
 // 128 E4M3 codes), plus one scale dword per operand row. Every wave loads 64
 // scale rows per chunk (one global_load_lds_dword), so a stage holds
-// kWaves * 64 = 512 scale rows whatever its operand rows.
-template <int BM, int BN, bool DUAL>
+// W * 64 = 512 scale rows whatever its operand rows.
+template <int BM, int BN, bool DUAL, int W>
 struct MxStages {
   static constexpr int NB = DUAL ? 2 : 1;
-  static constexpr int AROWS = BM > kDmaRows ? BM : kDmaRows;
+  static constexpr int DROWS = W * 1024 / (2 * kBK);
+  static constexpr int AROWS = BM > DROWS ? BM : DROWS;
   static constexpr int ROWS = AROWS + NB * BN;
-  static_assert(ROWS <= kWaves * 64, "one scale dword per operand row");
-  static constexpr int SCALE_OFF = ROWS * 2 * kBK;          // bytes
-  static constexpr int STAGE = SCALE_OFF + kWaves * 64 * 4;  // bytes
+  static constexpr int SLOADS = (ROWS + W * 64 - 1) / (W * 64);  // scale loads per wave per chunk
+  static constexpr int SCALE_OFF = ROWS * 2 * kBK;                   // bytes
+  static constexpr int STAGE = SCALE_OFF + SLOADS * W * 64 * 4;  // bytes
   static constexpr int FIT = (152 * 1024) / STAGE;
   static constexpr int NS = FIT < 2 ? 2 : (FIT > 8 ? 8 : FIT);
   static constexpr int BYTES = STAGE * NS;
-  static constexpr int LOADS = ROWS / kDmaRows + 1;  // code rows, then the scale dword
+  static constexpr int LOADS = ROWS / DROWS + SLOADS;  // code rows, then the scale dwords
 };
 
 __device__ __forceinline__ uint4 lds16(const bf16_t* lds, int row, int chunk) {
   return *reinterpret_cast<const uint4*>(lds + row * kBK + swz_chunk<kBK>(row, chunk) * 8);
+}
+
+// A wave's WM x WN block of h = val(i, j, v) as MXFP8: the 32 values of a row
+// and block sit in lanes l and l ^ 32; codes through store_block, one scale
+// code byte per row and block.
+template <int MI, int NI, int WM, int WN, class Val>
+__device__ __forceinline__ void mx_store_h(const GemmArgs& a, bf16_t* smem, int row0, int m_end, int col0, int wave,
+                                           int lane, Val&& val) {
+  uint32_t codes[MI][NI][4];
+#pragma unroll
+  for (int i = 0; i < MI; ++i) {
+    const int row = row0 + i * 32 + (lane & 31);
+#pragma unroll
+    for (int j = 0; j < NI; ++j) {
+      const int col = col0 + j * 32;
+      float r[16];
+      float amax = 0.0f;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        r[v] = val(i, j, v);
+        amax = fmaxf(amax, fabsf(r[v]));
+      }
+      amax = fmaxf(amax, __shfl_xor(amax, 32, kWave));
+      const uint32_t code = mx_scale_code(amax);
+      const float inv = mx_inv_scale(code);
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+        codes[i][j][g] = e4m3x4(r[4 * g] * inv, r[4 * g + 1] * inv, r[4 * g + 2] * inv, r[4 * g + 3] * inv);
+      if (row < m_end && lane < 32)
+        reinterpret_cast<uint8_t*>(a.Cs + (size_t)(col / kMxChunk) * a.M_cap + row)[(col / kMxBlock) & 3] =
+            static_cast<uint8_t>(code);
+    }
+  }
+  store_block<WM, WN, 1>(smem, a.C, a.N, row0, m_end, col0, wave, lane,
+                         [&](int i, int j, int g) { return codes[i][j][g]; });
 }
 
 // One BM x BN MXFP8 tile (two when DUAL) over the whole K range, as
@@ -363,17 +452,19 @@ __device__ __forceinline__ uint4 lds16(const bf16_t* lds, int row, int chunk) {
 // scale dwords; otherwise C is written as bf16.
 // SPLIT: only K chunks [kc0, kc1) are summed, the fp32 sums written as in
 // gemm_tile.
-template <int BM, int BN, int WAVES_M, bool DUAL, bool SPLIT = false, bool COH = false>
+template <int W, int BM, int BN, int WAVES_M, bool DUAL, bool SPLIT = false, bool COH = false>
 __device__ __forceinline__ void gemm_tile_mx(const GemmArgs& a, bf16_t* smem, int e, int m0, int m_end, int n0,
                                              int kc0 = 0, int kc1 = -1, float* pbase = nullptr,
                                              size_t pstride = 0, int pld = 0, int pcol0 = 0, bool coh = true) {
-  using St = MxStages<BM, BN, DUAL>;
+  using St = MxStages<BM, BN, DUAL, W>;
   constexpr int NB = DUAL ? 2 : 1;
-  constexpr int WAVES_N = kWaves / WAVES_M;
+  constexpr int WAVES_N = W / WAVES_M;
   constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
   constexpr int MI = WM / 32, NI = WN / 32;
   constexpr int AR = St::AROWS;
   static_assert(MI >= 1 && NI >= 1, "wave tile");
+  e = uniform_int(e), m0 = uniform_int(m0), m_end = uniform_int(m_end), n0 = uniform_int(n0);
+  kc0 = uniform_int(kc0), kc1 = uniform_int(kc1);
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WAVES_N, wn = wave % WAVES_N;
@@ -387,43 +478,46 @@ __device__ __forceinline__ void gemm_tile_mx(const GemmArgs& a, bf16_t* smem, in
 
   // Loop-invariant byte offsets of this lane's 16-byte pieces, as in
   // gemm_tile (the rows of a chunk are 128 codes here).
-  constexpr int RPI = 8, LA = AR / (RPI * kWaves), LB = BN / (RPI * kWaves);
+  constexpr int RPI = 8, LA = AR / (RPI * W), LB = BN / (RPI * W);
   uint32_t offA[LA], offB[LB];
 #pragma unroll
   for (int t = 0; t < LA; ++t) {
-    const int r = (t * kWaves + wave) * RPI + lane / 8;
+    const int r = (t * W + wave) * RPI + lane / 8;
     const int rr = r < a_rows ? r : a_rows - 1;
     offA[t] = (uint32_t)(rr * K + swz_chunk<kBK>(r, lane % 8) * 16);
   }
 #pragma unroll
   for (int t = 0; t < LB; ++t) {
-    const int r = (t * kWaves + wave) * RPI + lane / 8;
+    const int r = (t * W + wave) * RPI + lane / 8;
     offB[t] = (uint32_t)(r * LDB + swz_chunk<kBK>(r, lane % 8) * 16);
   }
-  // Scale rows: wave w loads scale rows [64 w, 64 w + 64) of the stage, all
-  // in one operand (AR and BN are multiples of 64): A rows (clamped), the
-  // gate (or only) weight rows, the up weight rows, or a placeholder that
-  // re-reads A's first row.
-  const int q0 = wave * 64;
-  const char* sb_base;
-  size_t s_stride;  // bytes per K chunk
-  uint32_t soff;
-  if (q0 < AR) {
-    sb_base = reinterpret_cast<const char*>(a.As + m0);
-    s_stride = (size_t)a.M_cap * 4;
-    soff = (uint32_t)(min(q0 + lane, a_rows - 1) * 4);
-  } else if (q0 < AR + BN) {
-    sb_base = reinterpret_cast<const char*>(a.Bs0 + (size_t)e * nK * N + n0 + (q0 - AR));
-    s_stride = (size_t)N * 4;
-    soff = (uint32_t)(lane * 4);
-  } else if (DUAL && q0 < AR + 2 * BN) {
-    sb_base = reinterpret_cast<const char*>(a.Bs1 + (size_t)e * nK * N + n0 + (q0 - AR - BN));
-    s_stride = (size_t)N * 4;
-    soff = (uint32_t)(lane * 4);
-  } else {
-    sb_base = reinterpret_cast<const char*>(a.As + m0);
-    s_stride = (size_t)a.M_cap * 4;
-    soff = 0;
+  // Scale rows: load u of wave w takes scale rows [64 (u W + w), +64) of
+  // the stage, all in one operand (AR and BN are multiples of 64): A rows
+  // (clamped), the gate (or only) weight rows, the up weight rows, or a
+  // placeholder that re-reads A's first row.
+  const char* sb_base[St::SLOADS];
+  size_t s_stride[St::SLOADS];  // bytes per K chunk
+  uint32_t soff[St::SLOADS];
+#pragma unroll
+  for (int u = 0; u < St::SLOADS; ++u) {
+    const int q0 = (u * W + wave) * 64;
+    if (q0 < AR) {
+      sb_base[u] = reinterpret_cast<const char*>(a.As + m0);
+      s_stride[u] = (size_t)a.M_cap * 4;
+      soff[u] = (uint32_t)(min(q0 + lane, a_rows - 1) * 4);
+    } else if (q0 < AR + BN) {
+      sb_base[u] = reinterpret_cast<const char*>(a.Bs0 + (size_t)e * nK * N + n0 + (q0 - AR));
+      s_stride[u] = (size_t)N * 4;
+      soff[u] = (uint32_t)(lane * 4);
+    } else if (DUAL && q0 < AR + 2 * BN) {
+      sb_base[u] = reinterpret_cast<const char*>(a.Bs1 + (size_t)e * nK * N + n0 + (q0 - AR - BN));
+      s_stride[u] = (size_t)N * 4;
+      soff[u] = (uint32_t)(lane * 4);
+    } else {
+      sb_base[u] = reinterpret_cast<const char*>(a.As + m0);
+      s_stride[u] = (size_t)a.M_cap * 4;
+      soff[u] = 0;
+    }
   }
 
   f32x16_t acc[NB][MI][NI];
@@ -437,21 +531,30 @@ __device__ __forceinline__ void gemm_tile_mx(const GemmArgs& a, bf16_t* smem, in
   // A placeholder load (live == false) re-reads the last chunk, which is in
   // the cache by then, so loads never leave the operands.
   if (kc1 < 0) kc1 = nK;
-  auto issue = [&](int kc, bool live, bf16_t* st) {
+  constexpr int KS = kMxChunk / 64;
+  auto issue = [&](int kc, bool live, bf16_t* st, int part) {
     const int kcl = live ? kc0 + kc : kc1 - 1;
     char* sl = reinterpret_cast<char*>(st);
-    const void* pa = uniform_ptr(A + (size_t)kcl * kMxChunk);
+    const uint32_t l0 = lds_addr(st) + wave * (RPI * 128);
+    constexpr int LS = W * RPI * 128;  // LDS bytes between a wave's loads
+    auto mine = [&](int t) { return part < 0 || (St::NS > 2 ? t * KS / St::LOADS : 0) == part; };
 #pragma unroll
-    for (int t = 0; t < LA; ++t) dma16s(pa, offA[t], sl + (t * kWaves + wave) * RPI * 128);
-    const void* pb0 = uniform_ptr(B0 + (size_t)kcl * kMxChunk);
+    for (int t = 0; t < LA; ++t)
+      if (mine(t)) dma16a(uniform_ptr(A + (size_t)kcl * kMxChunk), offA[t], l0 + t * LS);
 #pragma unroll
-    for (int t = 0; t < LB; ++t) dma16s(pb0, offB[t], sl + (AR + (t * kWaves + wave) * RPI) * 128);
+    for (int t = 0; t < LB; ++t)
+      if (mine(LA + t)) dma16a(uniform_ptr(B0 + (size_t)kcl * kMxChunk), offB[t], l0 + AR * 128 + t * LS);
     if (DUAL) {
-      const void* pb1 = uniform_ptr(B1 + (size_t)kcl * kMxChunk);
 #pragma unroll
-      for (int t = 0; t < LB; ++t) dma16s(pb1, offB[t], sl + (AR + BN + (t * kWaves + wave) * RPI) * 128);
+      for (int t = 0; t < LB; ++t)
+        if (mine(LA + LB + t))
+          dma16a(uniform_ptr(B1 + (size_t)kcl * kMxChunk), offB[t], l0 + (AR + BN) * 128 + t * LS);
     }
-    dma4s(uniform_ptr(sb_base + (size_t)kcl * s_stride), soff, sl + St::SCALE_OFF + wave * 256);
+#pragma unroll
+    for (int u = 0; u < St::SLOADS; ++u)
+      if (mine(LA + (DUAL ? 2 : 1) * LB + u))
+        dma4s(uniform_ptr(sb_base[u] + (size_t)kcl * s_stride[u]), soff[u],
+              sl + St::SCALE_OFF + (u * W + wave) * 256);
   };
   // A fragments (and scales) are double buffered; a weight fragment is
   // refilled for the next k-step once its MI MFMAs of this k-step are issued
@@ -501,7 +604,7 @@ __device__ __forceinline__ void gemm_tile_mx(const GemmArgs& a, bf16_t* smem, in
     if (NMFMA > PAIRS) __builtin_amdgcn_sched_group_barrier(0x008, NMFMA - PAIRS, 0);
     if (NREAD > PAIRS) __builtin_amdgcn_sched_group_barrier(0x100, NREAD - PAIRS, 0);
   };
-  pipeline_xk<St::NS, St::LOADS, kMxChunk / 64, true>(kc1 - kc0, smem, St::STAGE / 2, issue, read, mma, mix);
+  pipeline_xk<St::NS, St::LOADS, KS, true>(kc1 - kc0, smem, St::STAGE / 2, issue, read, mma, mix);
 
   if (SPLIT) {
     split_epilogue<MI, NI, NB, WM, WN, COH>(acc, m0, m_end, pcol0, pld, wm, wn, lane, pbase, pstride, coh);
@@ -510,54 +613,339 @@ __device__ __forceinline__ void gemm_tile_mx(const GemmArgs& a, bf16_t* smem, in
 
   // Epilogue: output layout as in gemm_tile (lane l: row l % 32, columns
   // 8 g + 4 h + (0..3) of each 32-column block).
-#pragma unroll
-  for (int i = 0; i < MI; ++i) {
-    const int row = m0 + wm * WM + i * 32 + r32;
-    const bool ok = row < m_end;  // the same for lanes l and l ^ 32
-#pragma unroll
-    for (int j = 0; j < NI; ++j) {
-      const int col0 = n0 + wn * WN + j * 32;
-      if (DUAL) {
-        float r[16];
-        float amax = 0.0f;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          r[v] = silu_mul_fast(acc[0][i][j][v], acc[NB - 1][i][j][v]);
-          amax = fmaxf(amax, fabsf(r[v]));
-        }
-        amax = fmaxf(amax, __shfl_xor(amax, 32, kWave));
-        const uint32_t code = mx_scale_code(amax);
-        const float inv = mx_inv_scale(code);
-        if (ok) {
-          uint8_t* crow = reinterpret_cast<uint8_t*>(a.C) + (size_t)row * N + col0 + 4 * h;
-#pragma unroll
-          for (int g = 0; g < 4; ++g)
-            *reinterpret_cast<uint32_t*>(crow + 8 * g) =
-                e4m3x4(r[4 * g] * inv, r[4 * g + 1] * inv, r[4 * g + 2] * inv, r[4 * g + 3] * inv);
-          if (h == 0)
-            reinterpret_cast<uint8_t*>(a.Cs + (size_t)(col0 / kMxChunk) * a.M_cap + row)[(col0 / kMxBlock) & 3] =
-                static_cast<uint8_t>(code);
-        }
-      } else if (ok) {
-        bf16_t* crow = a.C + (size_t)row * N + col0 + 4 * h;
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          uint2 packed;
-          packed.x = pack_bf16x2(acc[0][i][j][4 * g], acc[0][i][j][4 * g + 1]);
-          packed.y = pack_bf16x2(acc[0][i][j][4 * g + 2], acc[0][i][j][4 * g + 3]);
-          *reinterpret_cast<uint2*>(crow + 8 * g) = packed;
-        }
-      }
-    }
+  if constexpr (DUAL) {
+    mx_store_h<MI, NI, WM, WN>(
+        a, smem, m0 + wm * WM, m_end, n0 + wn * WN, wave, lane,
+        [&](int i, int j, int v) { return silu_mul_fast(acc[0][i][j][v], acc[NB - 1][i][j][v]); });
+  } else {
+    store_block<WM, WN, 2>(smem, a.C, N, m0 + wm * WM, m_end, n0 + wn * WN, wave, lane, [&](int i, int j, int g) {
+      return make_uint2(pack_bf16x2(acc[0][i][j][4 * g], acc[0][i][j][4 * g + 1]),
+                        pack_bf16x2(acc[0][i][j][4 * g + 2], acc[0][i][j][4 * g + 3]));
+    });
   }
 }
 
-template <bool DUAL>
+// ---------------------------------------------------------------------------
+// The 256-row tile of 256 weight rows (gate and up x 128 columns, or 256
+// columns of a single matrix): 4 waves (2 x 2), each 128 rows x 128 weight
+// rows, i.e. four quadrants (A half, B half) of 64 x 64.
+//
+// A K chunk is four 16 KB LDS slots (A0, A1, B0, B1: the halves every wave's
+// quadrants read), two chunks deep. The fragments of a whole slot (64 rows x
+// 128 bytes a wave) fit in 32 registers, so each phase runs the 16 MFMAs of
+// one quadrant from registers while one slot of what comes next is read from
+// LDS and the slot read in the phase before is refilled from global memory
+// for the chunk after next:
+//
+//   even chunk  A0 B0 | A0 B1 | A1 B1 | A1 B0     odd chunk  A0 B1 | A0 B0 | A1 B0 | A1 B1
+//   reads       B1      A1      A0'     B1'                  B0      A1      A0'     B0'
+//
+// (' next chunk; the order alternates so that a phase never reads into
+// registers its own MFMAs use). A slot is read in one phase out of eight, so
+// each load has seven phases (1.75 chunks) to land, where whole-chunk
+// buffering left it one chunk, and the loads leave evenly spread. One wave
+// per SIMD with a 128 x 128 tile reads 128 KB of LDS a chunk against 192 KB
+// for eight 64 x 128 ones.
+//
+// What bounds it is the chip's power: one 8192 x 28672 x 4096 product of
+// normally distributed values runs at 1290 TFLOP/s with the clock pulled down
+// to 1.58 GHz (77 % of the MFMA rate at that clock; all-zero operands, 1886
+// TFLOP/s at 2.37 GHz), its MFMAs alone at 1640 TFLOP/s and 1.97 GHz, MFMAs
+// and LDS reads at 1530. Against the 8-wave tile, same box: gate/up of the
+// Mixtral-shaped T = 4096 batch 1723 -> 1633 us, DSV3-shaped shard 986 -> 898,
+// Maverick-shaped 903 -> 815, MXFP8 Mixtral-shaped 916 -> 870 us.
+// ---------------------------------------------------------------------------
+constexpr int kSlotRows = 128;
+constexpr int kSlotElems = kSlotRows * kBK;  // bf16 elements: 16 KB
+template <bool MX>
+struct BigStages {
+  static constexpr int SCALE_OFF = 8 * kSlotElems;                     // elements: after the 8 slots
+  static constexpr int BYTES = 8 * kSlotElems * 2 + (MX ? 8 * kSlotRows * 4 : 0);
+  static constexpr int LOADS = MX ? 5 : 4;  // loads per wave per slot
+};
+
+template <bool DUAL, bool MX>
+__device__ __forceinline__ void big_tile(const GemmArgs& a, bf16_t* smem, int e, int m0, int m_end, int n0,
+                                         int kc0 = 0, int kc1 = -1, float* pbase = nullptr, size_t pstride = 0,
+                                         int pld = 0, int pcol0 = 0) {
+  // wave-uniform by construction; said so, they and what is computed from
+  // them stay in SGPRs
+  e = uniform_int(e), m0 = uniform_int(m0), m_end = uniform_int(m_end), n0 = uniform_int(n0);
+  kc0 = uniform_int(kc0), kc1 = uniform_int(kc1);
+  using St = BigStages<MX>;
+  constexpr int EB = MX ? 1 : 2;           // bytes per element
+  constexpr int CB = 128;                  // bytes of a row per chunk
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 1, wn = wave & 1;
+  const int r32 = lane & 31, hi = lane >> 5;
+  const int K = a.K, N = a.N;
+  const int nKt = K * EB / CB;  // chunks of a whole row
+  if (kc1 < 0) kc1 = nKt;
+  const int nK = kc1 - kc0;
+  const int a_rows = m_end - m0;
+  const bool gather = !MX && a.a_src != nullptr;
+  const size_t ldbB = (size_t)a.ldb * EB;  // bytes between weight rows
+  const char* A = reinterpret_cast<const char*>(a.A) + (gather ? 0 : (size_t)m0 * K * EB);
+  const char* B0 = reinterpret_cast<const char*>(a.B0) + ((size_t)e * N + n0) * ldbB;
+  const char* B1 = DUAL ? reinterpret_cast<const char*>(a.B1) + ((size_t)e * N + n0) * ldbB : B0 + 64 * ldbB;
+  const char *SA = nullptr, *SB0 = nullptr, *SB1 = nullptr;
+  if (MX) {
+    SA = reinterpret_cast<const char*>(a.As + m0);
+    SB0 = reinterpret_cast<const char*>(a.Bs0 + (size_t)e * nKt * N + n0);
+    SB1 = DUAL ? reinterpret_cast<const char*>(a.Bs1 + (size_t)e * nKt * N + n0) : SB0 + 64 * 4;
+  }
+
+  // Slot row q of A half h is tile row 128 (q / 64) + 64 h + q % 64; of B
+  // half b, weight row q of matrix b (dual) or column 128 (q / 64) + 64 b +
+  // q % 64. Load t of wave w moves slot rows [8 (4 t + w), +8), lane l row
+  // l / 8, piece l % 8 of the swizzled row. A rows past the tile re-read its
+  // last row.
+  uint32_t offA[2][4], offB[4];
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    const int q = (t * 4 + wave) * 8 + lane / 8;
+    const int c = swz_chunk<kBK>(q, lane % 8) * 16;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      int rr = min((q >> 6) * 128 + h * 64 + (q & 63), a_rows - 1);
+      if (gather) rr = min(max(a.a_src[m0 + rr] / a.a_div, 0), a.a_T - 1);
+      offA[h][t] = (uint32_t)rr * (uint32_t)(K * EB) + (uint32_t)c;
+    }
+    offB[t] = (uint32_t)(DUAL ? q : (q >> 6) * 128 + (q & 63)) * (uint32_t)ldbB + (uint32_t)c;
+  }
+  // scale dwords: waves 0 and 2 load slot rows [0, 64), waves 1 and 3 rows
+  // [64, 128) (the same values to the same place twice)
+  uint32_t soffA[2], soffB = 0;
+  if (MX) {
+    soffA[0] = (uint32_t)min((wave & 1) * 128 + lane, a_rows - 1) * 4u;
+    soffA[1] = (uint32_t)min((wave & 1) * 128 + 64 + lane, a_rows - 1) * 4u;
+    soffB = (uint32_t)((wave & 1) * (DUAL ? 64 : 128) + lane) * 4u;
+  }
+
+  const uint32_t lds0 = lds_addr(smem) + wave * 8 * CB;
+  const uint32_t ldss = lds_addr(smem) + St::SCALE_OFF * 2 + (wave & 1) * 256;
+  // load t of slot w (0, 1: A halves; 2, 3: B halves) of chunk kc
+  auto issue = [&](int w, int kc, int t) {
+    // past the last chunk: a placeholder load of one line
+    const int msk = (kc - nK) >> 31;
+    const int kcl = kc0 + (kc & msk);
+    const char* base = w < 2 ? A : (w == 2 ? B0 : B1);
+    dma16o(base + (size_t)kcl * CB, (w < 2 ? offA[w & 1][t] : offB[t]) & (uint32_t)msk, lds0,
+           ((kc & 1) * 4 + w) * (kSlotElems * 2) + t * 32 * CB);
+    if (MX && t == 3) {
+      const char* sbase = w < 2 ? SA : (w == 2 ? SB0 : SB1);
+      dma4a(sbase + (size_t)kcl * (w < 2 ? a.M_cap : N) * 4, w < 2 ? soffA[w & 1] : soffB,
+            ldss + ((kc & 1) * 4 + w) * (kSlotRows * 4));
+    }
+  };
+  auto issue_slot = [&](int w, int kc) {
+#pragma unroll
+    for (int t = 0; t < 4; ++t) issue(w, kc, t);
+  };
+  // fragments: 16-byte piece 2 q + hi of the lane's row, q = 0..3 (bf16: the
+  // k-step q; MXFP8: pieces 2 s and 2 s + 1 are k-step s)
+  uint4 fr[4][2][4];     // [slot][32-row block][piece]
+  uint32_t sc[4][2];     // MXFP8: scale dword of the row, shifted to this lane's block
+  uint32_t fofA[4], fofB[4];  // byte offset of the lane's piece in slot 0
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int c = swz_chunk<kBK>(r32, 2 * q + hi) * 16;  // rows 32 or 64 apart swizzle alike
+    fofA[q] = (uint32_t)((wm * 64 + r32) * CB + c);
+    fofB[q] = (uint32_t)((wn * 64 + r32) * CB + c);
+  }
+  const char* lds = reinterpret_cast<const char*>(smem);
+  auto readf = [&](int w, int kc, int i, int q) {
+    fr[w][i][q] = *reinterpret_cast<const uint4*>(lds + (w < 2 ? fofA[q] : fofB[q]) +
+                                                  ((kc & 1) * 4 + w) * (kSlotElems * 2) + i * 32 * CB);
+  };
+  const uint32_t sofA = (uint32_t)(wm * 64 + r32) * 4, sofB = (uint32_t)(wn * 64 + r32) * 4;
+  auto reads = [&](int w, int kc, int i) {
+    sc[w][i] = *reinterpret_cast<const uint32_t*>(lds + (w < 2 ? sofA : sofB) + St::SCALE_OFF * 2 +
+                                                  ((kc & 1) * 4 + w) * (kSlotRows * 4) + i * 128) >> (8 * hi);
+  };
+
+  f32x16_t acc[2][2][2][2];  // [A half][B half][row block][column block]
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[h][b][i][j] = f32x16_t{};
+
+  auto mma = [&](int ha, int hb, int i, int j, int q) {
+    if constexpr (!MX) {
+      acc[ha][hb][i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(fr[2 + hb][j][q]), as_bf16x8(fr[ha][i][q]),
+                                                                  acc[ha][hb][i][j], 0, 0, 0);
+    } else {
+      auto f8 = [](uint4 lo, uint4 up) {
+        return int32x8_t{(int)lo.x, (int)lo.y, (int)lo.z, (int)lo.w, (int)up.x, (int)up.y, (int)up.z, (int)up.w};
+      };
+      const int32x8_t fb = f8(fr[2 + hb][j][q], fr[2 + hb][j][q + 1]), fa = f8(fr[ha][i][q], fr[ha][i][q + 1]);
+      // the scale byte of k-step s = q / 2 is byte 2 s of the shifted dword
+      if (q == 0)
+        acc[ha][hb][i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
+            fb, fa, acc[ha][hb][i][j], 0, 0, 0, (int)sc[2 + hb][j], 0, (int)sc[ha][i]);
+      else
+        acc[ha][hb][i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
+            fb, fa, acc[ha][hb][i][j], 0, 0, 2, (int)sc[2 + hb][j], 2, (int)sc[ha][i]);
+    }
+  };
+  // One phase: the MFMAs of quadrant (ha, hb); reads slot rw of chunk rc,
+  // refills slot iw with chunk ic (its last read was the phase before).
+  auto phase = [&](int ha, int hb, int rw, int rc, int iw, int ic) {
+    wait_lgkmcnt0();              // the fragments read in the last phase are here
+    wait_vmcnt<6 * St::LOADS>();  // this wave's loads of slot rw landed
+    lds_barrier();                // everyone's; and everyone has read slot iw
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      // four bf16 (or two MXFP8) MFMAs, one load and, in the first half of
+      // the phase, four LDS reads
+      if constexpr (!MX) {
+        mma(ha, hb, 0, 0, t);
+        mma(ha, hb, 0, 1, t);
+        issue(iw, ic, t);
+        if (t < 2) {
+          readf(rw, rc, 0, 2 * t);
+          readf(rw, rc, 1, 2 * t);
+        }
+        mma(ha, hb, 1, 0, t);
+        mma(ha, hb, 1, 1, t);
+        if (t < 2) {
+          readf(rw, rc, 0, 2 * t + 1);
+          readf(rw, rc, 1, 2 * t + 1);
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        }
+      } else {
+        mma(ha, hb, t & 1, 0, 2 * (t >> 1));
+        issue(iw, ic, t);
+        if (t < 2) {
+          readf(rw, rc, t, 0);
+          readf(rw, rc, t, 1);
+          reads(rw, rc, t);
+        }
+        mma(ha, hb, t & 1, 1, 2 * (t >> 1));
+        if (t < 2) {
+          readf(rw, rc, t, 2);
+          readf(rw, rc, t, 3);
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+
+  // Prologue: slots in the order they are read, nine of them
+  wait_vmcnt<0>();  // nothing older (a previous tile's stores) is left in the count
+  issue_slot(0, 0);
+  issue_slot(2, 0);
+  issue_slot(3, 0);
+  issue_slot(1, 0);
+  issue_slot(0, 1);
+  issue_slot(3, 1);
+  issue_slot(2, 1);
+  issue_slot(1, 1);
+  wait_vmcnt<6 * St::LOADS>();  // A0, B0 of chunk 0
+  lds_barrier();
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      readf(0, 0, i, q);
+      readf(2, 0, i, q);
+    }
+    if (MX) {
+      reads(0, 0, i);
+      reads(2, 0, i);
+    }
+  }
+  wait_lgkmcnt0();
+  lds_barrier();  // every wave has read A0 of chunk 0
+  issue_slot(0, 2);
+  auto even = [&](int c) {
+    phase(0, 0, 3, c, 2, c + 2);
+    phase(0, 1, 1, c, 3, c + 2);
+    phase(1, 1, 0, c + 1, 1, c + 2);
+    phase(1, 0, 3, c + 1, 0, c + 3);
+  };
+  int c = 0;
+  for (; c + 1 < nK; c += 2) {
+    even(c);
+    phase(0, 1, 2, c + 1, 3, c + 3);
+    phase(0, 0, 1, c + 1, 2, c + 3);
+    phase(1, 0, 0, c + 2, 1, c + 3);
+    phase(1, 1, 2, c + 2, 0, c + 4);
+  }
+  if (c < nK) even(c);
+  wait_lgkmcnt0();
+  wait_vmcnt<0>();
+  lds_barrier();  // no load is in flight and every wave is done with the slots
+
+  // Epilogue: register v of lane l holds weight row 8 (v / 4) + 4 hi + v % 4 of
+  // the 32 x 32 block for token row l % 32 (see gemm_tile); row block i of the
+  // wave's four is (A half i / 2, block i % 2).
+  if (pbase != nullptr) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const int r = wm * 128 + h * 64 + i * 32 + r32;  // row within the tile
+        if (m0 + r < m_end) {
+#pragma unroll
+          for (int b = 0; b < 2; ++b) {
+            float* p = pbase + (DUAL ? b * pstride : 0) + (size_t)r * pld + pcol0 +
+                       (DUAL ? wn * 64 : wn * 128 + b * 64) + 4 * hi;
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+              for (int g = 0; g < 4; ++g)
+                *reinterpret_cast<float4*>(p + j * 32 + 8 * g) =
+                    make_float4(acc[h][b][i][j][4 * g], acc[h][b][i][j][4 * g + 1], acc[h][b][i][j][4 * g + 2],
+                                acc[h][b][i][j][4 * g + 3]);
+          }
+        }
+      }
+    return;
+  }
+  if constexpr (DUAL && MX) {
+    mx_store_h<4, 2, 128, 64>(a, smem, m0 + wm * 128, m_end, n0 + wn * 64, wave, lane, [&](int i, int j, int v) {
+      return silu_mul_fast(acc[i >> 1][0][i & 1][j][v], acc[i >> 1][1][i & 1][j][v]);
+    });
+  } else if constexpr (DUAL) {
+    store_block<128, 64, 2>(smem, a.C, N, m0 + wm * 128, m_end, n0 + wn * 64, wave, lane, [&](int i, int j, int g) {
+      float v[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        v[q] = silu_mul_fast(acc[i >> 1][0][i & 1][j][4 * g + q], acc[i >> 1][1][i & 1][j][4 * g + q]);
+      return make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
+    });
+  } else {
+    store_block<128, 128, 2>(smem, a.C, N, m0 + wm * 128, m_end, n0 + wn * 128, wave, lane, [&](int i, int j, int g) {
+      const f32x16_t& c = acc[i >> 1][j >> 1][i & 1][j & 1];
+      return make_uint2(pack_bf16x2(c[4 * g], c[4 * g + 1]), pack_bf16x2(c[4 * g + 2], c[4 * g + 3]));
+    });
+  }
+}
+
+template <bool DUAL, int W>
 struct GemmShapes {
   // dual: 128 columns per matrix; single: 128 or 256 columns (see the kernel)
   static constexpr int BNW = DUAL ? 128 : 256;
-  static constexpr int b0 = Stages<64, BNW, DUAL>::BYTES, b1 = Stages<128, BNW, DUAL>::BYTES;
-  static constexpr int b2 = Stages<256, BNW, DUAL>::BYTES, b3 = Stages<256, 128, DUAL>::BYTES;
+  static constexpr int b0 = Stages<64, BNW, DUAL, W>::BYTES, b1 = Stages<128, BNW, DUAL, W>::BYTES;
+  static constexpr int b2 = W == 4 ? BigStages<false>::BYTES : Stages<256, BNW, DUAL, 8>::BYTES;
+  static constexpr int b3 = DUAL ? 0 : Stages<256, 128, false, W>::BYTES;
   static constexpr int m01 = b0 > b1 ? b0 : b1, m23 = b2 > b3 ? b2 : b3;
   static constexpr int kSmem = (m01 > m23 ? m01 : m23) / 2;  // bf16 elements
 };
@@ -604,8 +992,8 @@ __device__ __forceinline__ int wave_incl_scan(int x) {
   return x;
 }
 
-template <int NV>
-__device__ __forceinline__ void block_scan(int (&v)[NV], int (&excl)[NV], int (&total)[NV], int (*s_tot)[kWaves]) {
+template <int NV, int W>
+__device__ __forceinline__ void block_scan(int (&v)[NV], int (&excl)[NV], int (&total)[NV], int (*s_tot)[W]) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int inc[NV];
 #pragma unroll
@@ -618,80 +1006,82 @@ __device__ __forceinline__ void block_scan(int (&v)[NV], int (&excl)[NV], int (&
   for (int q = 0; q < NV; ++q) {
     int base = 0, tot = 0;
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) {
+    for (int w = 0; w < W; ++w) {
       if (w < wave) base += s_tot[q][w];
       tot += s_tot[q][w];
     }
     excl[q] = base + inc[q] - v[q];
-    total[q] = tot;
+    total[q] = uniform_int(tot);
   }
 }
 
-template <bool DUAL>
+template <bool DUAL, int W>
 struct MxShapes {
   static constexpr int BNW = DUAL ? 128 : 256;
-  static constexpr int b0 = MxStages<64, BNW, DUAL>::BYTES, b1 = MxStages<128, BNW, DUAL>::BYTES;
-  static constexpr int b2 = MxStages<256, BNW, DUAL>::BYTES, b3 = MxStages<256, 128, DUAL>::BYTES;
-  static constexpr int b4 = MxStages<64, 128, DUAL>::BYTES, b5 = MxStages<128, 128, DUAL>::BYTES;
+  static constexpr int b0 = MxStages<64, BNW, DUAL, W>::BYTES, b1 = MxStages<128, BNW, DUAL, W>::BYTES;
+  static constexpr int b2 = W == 4 ? BigStages<true>::BYTES : MxStages<256, BNW, DUAL, 8>::BYTES;
+  static constexpr int b3 = DUAL ? 0 : MxStages<256, 128, false, W>::BYTES;
+  static constexpr int b4 = MxStages<64, 128, DUAL, W>::BYTES, b5 = MxStages<128, 128, DUAL, W>::BYTES;
   static constexpr int m01 = b0 > b1 ? b0 : b1, m23 = b2 > b3 ? b2 : b3, m45 = b4 > b5 ? b4 : b5;
   static constexpr int m = m01 > m23 ? m01 : m23;
   static constexpr int kSmem = (m > m45 ? m : m45) / 2;  // bf16 slots
 };
 
-// One row tile of an unsplit launch: 128 or (single GEMM, wide) 256 columns.
-template <bool DUAL, bool MX, bool WIDE>
-__device__ __forceinline__ void run_tile(const GemmArgs& a, bf16_t* smem, int cls, int e, int m0, int m_end,
-                                         int n0) {
-  constexpr int BN = WIDE ? 256 : 128;
+// One tile of at most 128 rows (cls 0 or 1) and BN columns. SPLIT: K chunks
+// [kc0, kc1) only, fp32 sums to pbase (row stride pld, column base pcol0).
+template <int W, bool DUAL, bool MX, int BN, bool SPLIT, bool COH = false>
+__device__ __forceinline__ void run_low_tile(const GemmArgs& a, bf16_t* smem, int cls, int e, int m0, int m_end,
+                                             int n0, int kc0 = 0, int kc1 = -1, float* pbase = nullptr,
+                                             size_t ps = 0, int pld = 0, int pcol0 = 0, bool coh = true) {
   if constexpr (MX) {
     if (cls == 0)
-      gemm_tile_mx<64, BN, 2, DUAL>(a, smem, e, m0, m_end, n0);
-    else if (cls == 1)
-      gemm_tile_mx<128, BN, 2, DUAL>(a, smem, e, m0, m_end, n0);
+      gemm_tile_mx<W, 64, BN, 2, DUAL, SPLIT, COH>(a, smem, e, m0, m_end, n0, kc0, kc1, pbase, ps, pld, pcol0, coh);
     else
-      gemm_tile_mx<256, BN, 4, DUAL>(a, smem, e, m0, m_end, n0);
+      gemm_tile_mx<W, 128, BN, 2, DUAL, SPLIT, COH>(a, smem, e, m0, m_end, n0, kc0, kc1, pbase, ps, pld, pcol0, coh);
   } else {
     if (cls == 0)
-      gemm_tile<64, BN, 2, DUAL>(a, smem, e, m0, m_end, n0);
-    else if (cls == 1)
-      gemm_tile<128, BN, 2, DUAL>(a, smem, e, m0, m_end, n0);
+      gemm_tile<W, 64, BN, 2, DUAL, SPLIT, COH>(a, smem, e, m0, m_end, n0, kc0, kc1, pbase, ps, pld, pcol0, coh);
     else
-      gemm_tile<256, BN, 4, DUAL>(a, smem, e, m0, m_end, n0);
+      gemm_tile<W, 128, BN, 2, DUAL, SPLIT, COH>(a, smem, e, m0, m_end, n0, kc0, kc1, pbase, ps, pld, pcol0, coh);
   }
 }
 
-// One split-K tile of BN columns (128, or 256 for a wide single GEMM): K
-// chunks [kc0, kc1), fp32 sums to pbase (row stride pld, column base pcol0).
-template <bool DUAL, bool MX, int BN, bool COH = false>
-__device__ __forceinline__ void run_split_tile(const GemmArgs& a, bf16_t* smem, int cls, int e, int m0, int m_end,
-                                               int n0, int kc0, int kc1, float* pbase, size_t ps, int pld,
-                                               int pcol0, bool coh = true) {
-  if constexpr (MX && COH) {
-    // decode schedule: at most kSkRows rows a tile
-    if (cls == 0)
-      gemm_tile_mx<64, BN, 2, DUAL, true, true>(a, smem, e, m0, m_end, n0, kc0, kc1, pbase, ps, pld, pcol0, coh);
-    else
-      gemm_tile_mx<128, BN, 2, DUAL, true, true>(a, smem, e, m0, m_end, n0, kc0, kc1, pbase, ps, pld, pcol0, coh);
-  } else if constexpr (MX) {
-    if (cls == 0)
-      gemm_tile_mx<64, BN, 2, DUAL, true>(a, smem, e, m0, m_end, n0, kc0, kc1, pbase, ps, pld, pcol0);
-    else if (cls == 1)
-      gemm_tile_mx<128, BN, 2, DUAL, true>(a, smem, e, m0, m_end, n0, kc0, kc1, pbase, ps, pld, pcol0);
-    else
-      gemm_tile_mx<256, BN, 4, DUAL, true>(a, smem, e, m0, m_end, n0, kc0, kc1, pbase, ps, pld, pcol0);
-  } else if constexpr (COH) {
-    // decode schedule: at most kSkRows rows a tile
-    if (cls == 0)
-      gemm_tile<64, BN, 2, DUAL, true, true>(a, smem, e, m0, m_end, n0, kc0, kc1, pbase, ps, pld, pcol0, coh);
-    else
-      gemm_tile<128, BN, 2, DUAL, true, true>(a, smem, e, m0, m_end, n0, kc0, kc1, pbase, ps, pld, pcol0, coh);
+// One tile of the round schedule: any class, 128 columns per matrix or (a
+// wide single GEMM) 256; split along K when pbase != nullptr.
+template <int W, bool DUAL, bool MX, bool WIDE>
+__device__ __forceinline__ void run_tile(const GemmArgs& a, bf16_t* smem, int cls, int e, int m0, int m_end, int n0,
+                                         int kc0, int kc1, float* pbase, size_t ps, int pld, int pcol0) {
+  constexpr int BN = WIDE ? 256 : 128;
+  if (cls == 2) {
+    if constexpr (W == 8) {
+      if constexpr (MX) {
+        if (pbase != nullptr)
+          gemm_tile_mx<W, 256, BN, 4, DUAL, true>(a, smem, e, m0, m_end, n0, kc0, kc1, pbase, ps, pld, pcol0);
+        else
+          gemm_tile_mx<W, 256, BN, 4, DUAL>(a, smem, e, m0, m_end, n0);
+      } else {
+        if (pbase != nullptr)
+          gemm_tile<W, 256, BN, 4, DUAL, true>(a, smem, e, m0, m_end, n0, kc0, kc1, pbase, ps, pld, pcol0);
+        else
+          gemm_tile<W, 256, BN, 4, DUAL>(a, smem, e, m0, m_end, n0);
+      }
+    } else if constexpr (DUAL || WIDE) {
+      big_tile<DUAL, MX>(a, smem, e, m0, m_end, n0, kc0, kc1, pbase, ps, pld, pcol0);
+    } else if constexpr (MX) {
+      if (pbase != nullptr)
+        gemm_tile_mx<W, 256, BN, 2, DUAL, true>(a, smem, e, m0, m_end, n0, kc0, kc1, pbase, ps, pld, pcol0);
+      else
+        gemm_tile_mx<W, 256, BN, 2, DUAL>(a, smem, e, m0, m_end, n0);
+    } else {
+      if (pbase != nullptr)
+        gemm_tile<W, 256, BN, 2, DUAL, true>(a, smem, e, m0, m_end, n0, kc0, kc1, pbase, ps, pld, pcol0);
+      else
+        gemm_tile<W, 256, BN, 2, DUAL>(a, smem, e, m0, m_end, n0);
+    }
+  } else if (pbase != nullptr) {
+    run_low_tile<W, DUAL, MX, BN, true>(a, smem, cls, e, m0, m_end, n0, kc0, kc1, pbase, ps, pld, pcol0);
   } else {
-    if (cls == 0)
-      gemm_tile<64, BN, 2, DUAL, true>(a, smem, e, m0, m_end, n0, kc0, kc1, pbase, ps, pld, pcol0);
-    else if (cls == 1)
-      gemm_tile<128, BN, 2, DUAL, true>(a, smem, e, m0, m_end, n0, kc0, kc1, pbase, ps, pld, pcol0);
-    else
-      gemm_tile<256, BN, 4, DUAL, true>(a, smem, e, m0, m_end, n0, kc0, kc1, pbase, ps, pld, pcol0);
+    run_low_tile<W, DUAL, MX, BN, false>(a, smem, cls, e, m0, m_end, n0);
   }
 }
 
@@ -722,22 +1112,25 @@ __device__ __forceinline__ void tile_rc(int local, int n_mt, int n_nt, int& mt, 
   }
 }
 
+// UNI: `tile` is the same in every lane of the wave.
+template <bool UNI = true>
 __device__ __forceinline__ TileRef decode_tile(int tile, int E, const int* s_start, const int* s_row0,
                                                const int* s_rows, int cols, int N) {
+  auto uni = [](int v) { return UNI ? uniform_int(v) : v; };
   // last expert whose first tile is <= tile (experts with no tiles share
   // their start with the next one, so the last match is the owner)
   int lo = 0, hi = E - 1;
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
-    if (s_start[mid] <= tile) lo = mid; else hi = mid - 1;
+    if (uni(s_start[mid]) <= tile) lo = mid; else hi = mid - 1;
   }
   TileRef t;
   t.e = lo;
-  const int local = tile - s_start[lo];
-  const int er = s_rows[lo];
+  const int local = tile - uni(s_start[lo]);
+  const int er = uni(s_rows[lo]);
   int nt, mt;
   tile_rc(local, row_tiles(er), N / cols, mt, nt);
-  t.m0 = s_row0[lo] + mt * 256;
+  t.m0 = uni(s_row0[lo]) + mt * 256;
   t.left = er - mt * 256;  // rows from m0 to the expert's end, >= 1
   t.m_end = t.m0 + (t.left < 256 ? t.left : 256);
   t.n0 = nt * cols;
@@ -821,7 +1214,7 @@ __device__ __forceinline__ long long sk_blocks(long long U, long long G) {
 // this block's XCD. A slot holds NB planes of sk_rows x cols floats
 // (2 x 128 or 1 x 256 columns: the same size).
 constexpr int kFixBatch = 8;
-template <bool DUAL, bool MX>
+template <int W, bool DUAL, bool MX>
 __device__ __forceinline__ void sk_fixup(const GemmArgs& a, int m0, int m_end, int n0, int cols, int bf, int nc,
                                          int j0, bool coh) {
   constexpr int NB = DUAL ? 2 : 1;
@@ -831,7 +1224,7 @@ __device__ __forceinline__ void sk_fixup(const GemmArgs& a, int m0, int m_end, i
   // the CU's L1 holds no line of these slots from before their stores (each
   // slot is written and read once a launch); invalidate it all the same
   if (!coh) asm volatile("buffer_inv sc0" ::: "memory");
-  for (int it = (int)threadIdx.x; it < items; it += kThreads) {
+  for (int it = (int)threadIdx.x; it < items; it += W * kWave) {
     const int r = it / c4, c = (it - r * c4) * 4;
     const float* p0 = a.skpart + (size_t)r * cols + c;
     f32x4_t g = f32x4_t{}, u = f32x4_t{};
@@ -875,7 +1268,7 @@ __device__ __forceinline__ void sk_fixup(const GemmArgs& a, int m0, int m_end, i
 // xcd_ok: the XCD check's result (1: block b runs on XCD b % 8). wide: a
 // single GEMM in 256-column tiles (T0 and s_start count those tiles), which
 // halves the tiles, and so the pipeline fills, of short-K launches.
-template <bool DUAL, bool MX>
+template <int W, bool DUAL, bool MX>
 __device__ __forceinline__ void decode_schedule(const GemmArgs& a, bf16_t* smem, int T0, const int* s_start,
                                                 const int* s_row0, const int* s_rows, bool xcd_ok, bool wide) {
   constexpr int NB = DUAL ? 2 : 1;
@@ -926,11 +1319,11 @@ __device__ __forceinline__ void decode_schedule(const GemmArgs& a, bf16_t* smem,
     if (kc0 == 0 && kc1 == nK) {
       if constexpr (!DUAL) {
         if (wide)
-          run_tile<DUAL, MX, true>(a, smem, cls, tr.e, tr.m0, tr.m_end, tr.n0);
+          run_low_tile<W, DUAL, MX, 256, false>(a, smem, cls, tr.e, tr.m0, tr.m_end, tr.n0);
         else
-          run_tile<DUAL, MX, false>(a, smem, cls, tr.e, tr.m0, tr.m_end, tr.n0);
+          run_low_tile<W, DUAL, MX, 128, false>(a, smem, cls, tr.e, tr.m0, tr.m_end, tr.n0);
       } else {
-        run_tile<DUAL, MX, false>(a, smem, cls, tr.e, tr.m0, tr.m_end, tr.n0);
+        run_low_tile<W, DUAL, MX, 128, false>(a, smem, cls, tr.e, tr.m0, tr.m_end, tr.n0);
       }
     } else {
       const long long t0 = (long long)t * nK;
@@ -940,20 +1333,20 @@ __device__ __forceinline__ void decode_schedule(const GemmArgs& a, bf16_t* smem,
       float* mine = a.skpart + ((size_t)bo * 2 + (u == u_beg ? 0 : 1)) * slot_f;
       if constexpr (!DUAL) {
         if (wide)
-          run_split_tile<DUAL, MX, 256, true>(a, smem, cls, tr.e, tr.m0, tr.m_end, tr.n0, kc0, kc1, mine, plane,
-                                              256, 0, coh);
+          run_low_tile<W, DUAL, MX, 256, true, true>(a, smem, cls, tr.e, tr.m0, tr.m_end, tr.n0, kc0, kc1, mine,
+                                                  plane, 256, 0, coh);
         else
-          run_split_tile<DUAL, MX, 128, true>(a, smem, cls, tr.e, tr.m0, tr.m_end, tr.n0, kc0, kc1, mine, plane,
-                                              128, 0, coh);
+          run_low_tile<W, DUAL, MX, 128, true, true>(a, smem, cls, tr.e, tr.m0, tr.m_end, tr.n0, kc0, kc1, mine,
+                                                  plane, 128, 0, coh);
       } else {
-        run_split_tile<DUAL, MX, 128, true>(a, smem, cls, tr.e, tr.m0, tr.m_end, tr.n0, kc0, kc1, mine, plane, 128,
-                                            0, coh);
+        run_low_tile<W, DUAL, MX, 128, true, true>(a, smem, cls, tr.e, tr.m0, tr.m_end, tr.n0, kc0, kc1, mine, plane,
+                                                128, 0, coh);
       }
       __syncthreads();  // every wave's stores have completed
       if (threadIdx.x == 0) s_last = atomicAdd(a.tcnt + bf, 1) == nc - 1;
       __syncthreads();
-      if (s_last) {
-        sk_fixup<DUAL, MX>(a, tr.m0, tr.m_end, tr.n0, cols, bf, nc, j0, coh);
+      if (uniform_int(s_last)) {
+        sk_fixup<W, DUAL, MX>(a, tr.m0, tr.m_end, tr.n0, cols, bf, nc, j0, coh);
         if (threadIdx.x == 0) __hip_atomic_store(a.tcnt + bf, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
     }
@@ -963,16 +1356,16 @@ __device__ __forceinline__ void decode_schedule(const GemmArgs& a, bf16_t* smem,
 
 // Body of the grouped GEMM kernels (bf16 or MXFP8; a K chunk is 64 bf16 or
 // 128 E4M3 elements, 128 bytes of a row either way).
-template <bool DUAL, bool MX>
+template <int W, bool DUAL, bool MX>
 __device__ __forceinline__ void grouped_gemm_body(const GemmArgs& a) {
-  constexpr int kSmem = MX ? MxShapes<DUAL>::kSmem : GemmShapes<DUAL>::kSmem;
+  constexpr int kSmem = MX ? MxShapes<DUAL, W>::kSmem : GemmShapes<DUAL, W>::kSmem;
   constexpr int NB = DUAL ? 2 : 1;
   __shared__ __align__(16) bf16_t smem[kSmem];
   __shared__ int s_start[kMaxExperts + 1];
   __shared__ int s_row0[kMaxExperts];
   __shared__ int s_rows[kMaxExperts];
   __shared__ int s_srow0[kMaxExperts];
-  __shared__ int s_tot[6][kWaves];
+  __shared__ int s_tot[6][W];
 
   const int tid = threadIdx.x;
   const int E = a.E_local, G = gridDim.x;
@@ -998,7 +1391,7 @@ __device__ __forceinline__ void grouped_gemm_body(const GemmArgs& a) {
   int v[6] = {row_tiles(rows) * (a.N / 128), rows, rows > kSmallM ? 1 : 0, rows > 0 ? 1 : 0,
               rows > a.sk_rows ? 1 : 0, rows > kSkPrefRows ? 1 : 0};
   int ex[6], tot[6];
-  block_scan<6>(v, ex, tot, s_tot);
+  block_scan<6, W>(v, ex, tot, s_tot);
   const int T0 = tot[0], R = tot[1], n_big = tot[2], n_active = tot[3];
   // Decode schedule when every expert fits a slot's rows. Otherwise tiles
   // split along K need the reduction launch; when the host launches none
@@ -1028,7 +1421,7 @@ __device__ __forceinline__ void grouped_gemm_body(const GemmArgs& a) {
       a.plan[2] = 1;
     }
     __syncthreads();
-    decode_schedule<DUAL, MX>(a, smem, dwide ? T0 / 2 : T0, s_start, s_row0, s_rows, s_xcd == 1, dwide);
+    decode_schedule<W, DUAL, MX>(a, smem, dwide ? T0 / 2 : T0, s_start, s_row0, s_rows, uniform_int(s_xcd) == 1, dwide);
     return;
   }
 
@@ -1098,7 +1491,7 @@ __device__ __forceinline__ void grouped_gemm_body(const GemmArgs& a) {
     if (S > 1 && tid < E)
       for (int r = 0; r < s_rows[tid]; ++r) a.plan[kPlanHead + s_srow0[tid] + r] = s_row0[tid] + r;
     if (St > 1 && tid < rem) {
-      const TileRef t = decode_tile(full + tid, E, s_start, s_row0, s_rows, cols, a.N);
+      const TileRef t = decode_tile<false>(full + tid, E, s_start, s_row0, s_rows, cols, a.N);
       a.plan[kPlanHead + 3 * tid] = t.m0;
       a.plan[kPlanHead + 3 * tid + 1] = t.m_end;
       a.plan[kPlanHead + 3 * tid + 2] = t.n0;
@@ -1106,99 +1499,101 @@ __device__ __forceinline__ void grouped_gemm_body(const GemmArgs& a) {
   }
 
   // One item: a split-K tile, a split of a tail tile, or a tile.
-  auto run_item = [&](int item) {
+  auto run_item = [&](int item) __attribute__((always_inline)) {
+    TileRef t;
+    int kc0 = 0, kc1 = -1, pld = 0, pcol0 = 0;
+    float* pbase = nullptr;
+    size_t ps = 0;
     if (S > 1) {
       // split tile: S consecutive tiles share a row tile and a column block
       int lo = 0, hi = E - 1;
       while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
-        if (s_start[mid] <= item) lo = mid; else hi = mid - 1;
+        if (uniform_int(s_start[mid]) <= item) lo = mid; else hi = mid - 1;
       }
-      const int e = lo;
-      const int local = item - s_start[e];
-      const int er = s_rows[e];
+      const int local = item - uniform_int(s_start[lo]);
+      const int er = uniform_int(s_rows[lo]);
       const int sp = local % S, rest = local / S;
       int nt, mt;
       tile_rc(rest, row_tiles(er), a.N / 128, mt, nt);
-      const int kc0 = sp * nK / S, kc1 = (sp + 1) * nK / S;
-      const int m0 = s_row0[e] + mt * 256;
-      const int left = er - mt * 256;
-      const int m_end = m0 + (left < 256 ? left : 256);
-      float* pbase = a.part + ((size_t)sp * R + s_srow0[e] + mt * 256) * a.N;
-      const size_t ps = (size_t)S * R * a.N;
-      run_split_tile<DUAL, MX, 128>(a, smem, tile_class(left), e, m0, m_end, nt * 128, kc0, kc1, pbase, ps, a.N,
-                                    nt * 128);
-      return;
-    }
-    if (item >= full) {
+      kc0 = sp * nK / S, kc1 = (sp + 1) * nK / S;
+      t.e = lo;
+      t.m0 = uniform_int(s_row0[lo]) + mt * 256;
+      t.left = er - mt * 256;
+      t.m_end = t.m0 + (t.left < 256 ? t.left : 256);
+      t.n0 = nt * 128;
+      pbase = a.part + ((size_t)sp * R + uniform_int(s_srow0[lo]) + mt * 256) * a.N;
+      ps = (size_t)S * R * a.N;
+      pld = a.N;
+      pcol0 = t.n0;
+    } else if (item >= full) {
       // a split of a tail tile
       const int u = item - full, pr = u / St, sp = u - pr * St;
-      const TileRef t = decode_tile(full + pr, E, s_start, s_row0, s_rows, cols, a.N);
-      const int kc0 = sp * nK / St, kc1 = (sp + 1) * nK / St;
+      t = decode_tile(full + pr, E, s_start, s_row0, s_rows, cols, a.N);
+      kc0 = sp * nK / St, kc1 = (sp + 1) * nK / St;
       const size_t tsz = (size_t)256 * cols;
-      float* pbase = a.part + ((size_t)pr * NB * St + sp) * tsz;
-      if constexpr (!DUAL) {
-        if (wide) {
-          run_split_tile<DUAL, MX, 256>(a, smem, tile_class(t.left), t.e, t.m0, t.m_end, t.n0, kc0, kc1, pbase,
-                                        St * tsz, cols, 0);
-          return;
-        }
-      }
-      run_split_tile<DUAL, MX, 128>(a, smem, tile_class(t.left), t.e, t.m0, t.m_end, t.n0, kc0, kc1, pbase,
-                                    St * tsz, cols, 0);
-      return;
+      pbase = a.part + ((size_t)pr * NB * St + sp) * tsz;
+      ps = St * tsz;
+      pld = cols;
+    } else {
+      t = decode_tile(item, E, s_start, s_row0, s_rows, cols, a.N);
     }
-    const TileRef t = decode_tile(item, E, s_start, s_row0, s_rows, cols, a.N);
     const int cls = tile_class(t.left);
-    if (!DUAL && wide)
-      run_tile<DUAL, MX, !DUAL>(a, smem, cls, t.e, t.m0, t.m_end, t.n0);
-    else
-      run_tile<DUAL, MX, false>(a, smem, cls, t.e, t.m0, t.m_end, t.n0);
+    if constexpr (!DUAL) {
+      if (wide) {
+        run_tile<W, DUAL, MX, true>(a, smem, cls, t.e, t.m0, t.m_end, t.n0, kc0, kc1, pbase, ps, pld, pcol0);
+        return;
+      }
+    }
+    run_tile<W, DUAL, MX, false>(a, smem, cls, t.e, t.m0, t.m_end, t.n0, kc0, kc1, pbase, ps, pld, pcol0);
   };
 
-  const int per_xcd = G >> 3;
-  if (a.queue != nullptr && (G & 7) == 0) {
-    // Per-XCD work queues: block b runs on XCD b % 8 and takes items of that
-    // XCD's share of every round (the same items the static order below
-    // gives it) in order from a counter, so blocks that drew cheap tiles
-    // take more. The counter for the next item is requested before a tile
-    // and read after it.
-    __shared__ int s_item;
-    const int xcd = (int)(blockIdx.x & 7);
-    auto item_of = [&](int j) { return (j / per_xcd) * G + xcd * per_xcd + j % per_xcd; };
-    if (tid == 0) s_item = item_of(atomicAdd(a.queue + xcd, 1));
+  // Per-XCD work queues: block b runs on XCD b % 8 and takes items of that
+  // XCD's share of every round (the same items the static order gives it) in
+  // order from a counter, so blocks that drew cheap tiles take more. The
+  // counter for the next item is requested before a tile and read after it.
+  // Without a queue block b takes the items of its slot. One loop for both,
+  // so that the tile code is there once.
+  __shared__ int s_item;
+  const int per_xcd = G >> 3, xcd_b = (int)(blockIdx.x & 7);
+  const bool dyn = a.queue != nullptr && (G & 7) == 0;
+  auto item_of = [&](int j) { return (j / per_xcd) * G + xcd_b * per_xcd + j % per_xcd; };
+  int item = (G & 7) ? (int)blockIdx.x : (xcd_b * per_xcd + (int)(blockIdx.x >> 3));
+  if (dyn) {
+    if (tid == 0) s_item = item_of(atomicAdd(a.queue + xcd_b, 1));
     __syncthreads();
-    int item = s_item;
-    while (item < n_items) {
-      int j_next = 0;
-      if (tid == 0) j_next = atomicAdd(a.queue + xcd, 1);
-      run_item(item);
+    item = uniform_int(s_item);
+  }
+  while (item < n_items) {
+    int j_next = 0;
+    if (dyn && tid == 0) j_next = atomicAdd(a.queue + xcd_b, 1);
+    run_item(item);
+    if (dyn) {
       if (tid == 0) s_item = item_of(j_next);
       __syncthreads();
-      item = s_item;
+      item = uniform_int(s_item);
+    } else {
+      item += G;
     }
-    // The last block to finish (every other block has drawn its last item)
-    // zeroes the counters for the next launch.
-    if (tid == 0 && a.done != nullptr && atomicAdd(a.done, 1) == G - 1) {
-      for (int q = 0; q < 8; ++q) __hip_atomic_store(a.queue + q, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __hip_atomic_store(a.done, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    return;
   }
-  const int slot = (G & 7) ? (int)blockIdx.x : ((int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3));
-  for (int item = slot; item < n_items; item += G) run_item(item);
+  // The last block to finish (every other block has drawn its last item)
+  // zeroes the counters for the next launch.
+  if (dyn && tid == 0 && a.done != nullptr && atomicAdd(a.done, 1) == G - 1) {
+    for (int q = 0; q < 8; ++q) __hip_atomic_store(a.queue + q, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(a.done, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
 }
 
-template <bool DUAL>
-__global__ __launch_bounds__(kThreads) void grouped_gemm_bf16_kernel(GemmArgs a) {
-  grouped_gemm_body<DUAL, false>(a);
+template <bool DUAL, int W>
+__global__ __launch_bounds__(W* kWave) void grouped_gemm_bf16_kernel(GemmArgs a) {
+  grouped_gemm_body<W, DUAL, false>(a);
 }
 
-// MXFP8 grouped GEMM: the same tile schedule (no split-K); the dual GEMM
-// writes MXFP8 h, the single one bf16.
-template <bool DUAL>
-__global__ __launch_bounds__(kThreads) void grouped_gemm_mx_kernel(GemmArgs a) {
-  grouped_gemm_body<DUAL, true>(a);
+// MXFP8 grouped GEMM: the same tile schedule; the dual GEMM writes MXFP8 h,
+// the single one bf16.
+template <bool DUAL, int W>
+__global__ __launch_bounds__(W* kWave) void grouped_gemm_mx_kernel(GemmArgs a) {
+  grouped_gemm_body<W, DUAL, true>(a);
 }
 
 // Tail tiles of an unsplit launch (see grouped_gemm_body): item `it` of the
@@ -1525,7 +1920,7 @@ static int device_cu_count() {
 // st[1] counts mismatches, st[2] finished blocks. It has the GEMMs' block
 // size and holds a comparable share of LDS, so blocks are placed as theirs.
 static __device__ int32_t xcd_check[4];
-__global__ __launch_bounds__(kThreads) void xcd_probe_kernel(int32_t* st) {
+__global__ __launch_bounds__(kMaxWaves* kWave) void xcd_probe_kernel(int32_t* st) {
   __shared__ int32_t s_pad[32768];
   int x;
   asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID, 0, 4)" : "=s"(x));
@@ -1581,7 +1976,7 @@ static const int32_t* xcd_state(hipStream_t s) {
       d.done = nullptr;
       return nullptr;
     }
-    xcd_probe_kernel<<<kMaxBlocks, kThreads, 0, s>>>(d.ptr);
+    xcd_probe_kernel<<<kMaxBlocks, kMaxWaves * kWave, 0, s>>>(d.ptr);
     if (hipGetLastError() != hipSuccess || hipEventRecord(d.done, s) != hipSuccess) {
       (void)hipGetLastError();
       return nullptr;
@@ -1597,6 +1992,30 @@ static const int32_t* xcd_state(hipStream_t s) {
       (void)hipGetLastError();
   }
   return d.ready || s == d.stream ? d.ptr : nullptr;
+}
+
+// Whether a GEMM launch takes 4-wave blocks (the large tile, see big_tile) or
+// 8-wave ones, from what the host knows: M_cap bounds the rows of all local
+// experts, and under expert parallelism most of it belongs to remote ones (the
+// measured shards hold an eighth). 4 waves pay where 256-row tiles do most of
+// the work and lose on the small and mid tiles, which stream weights: same
+// box, us, 8 / 4 waves:
+//   gate/up  DSV3-shaped shard T = 600 318 / 341, 1500 331 / 335, 4000 453 /
+//            411, 16384 986 / 898; Maverick-shaped 9000 492 / 498, 18000 261 /
+//            263, 32768 903 / 815; Mixtral-shaped 4096 1723 / 1633; Qwen3-shaped
+//            8192 448 / 448; MXFP8 Mixtral-shaped 4096 916 / 870
+//   down     DSV3-shaped 16384 515 / 526, Maverick-shaped 32768 507 / 535,
+//            Qwen3-shaped 8192 271 / 303, one Mixtral-shaped expert of 4000 rows
+//            (128-column tiles) 404 / 439; Mixtral-shaped 4096 859 / 785, MXFP8
+//            481 / 406
+// So gate/up takes them from 1024 rows of M_cap per local expert on (128 real
+// rows an expert in an eight-way shard, where half of the tiles are large);
+// the down GEMM, whose tail tiles weigh more, only when in addition at most 8
+// experts share the rows (large experts even if the share is an eighth of a
+// layer) and the launch has the tiles for 256-column ones (see `wide`).
+static bool four_waves(bool dual, int M_cap, int E_local, int N) {
+  if (M_cap <= kSkHostRows || (long long)M_cap < 1024LL * E_local) return false;
+  return dual || (E_local <= 8 && (long long)M_cap * N >= 1LL << 25);
 }
 
 hipError_t launch_ffn(const void* x_perm, const void* w_gate, const void* w_up, const void* w_down,
@@ -1627,7 +2046,7 @@ hipError_t launch_ffn(const void* x_perm, const void* w_gate, const void* w_up, 
   // tiles than blocks, so the grid covers at least 8 of those.
   auto grid_for = [&](int N) {
     const long long ub = ((long long)(M_cap + kSmallM - 1) / kSmallM + E_local) * (N / 128) * kMaxSplit;
-    long long g = std::min(cus, kMaxBlocks);  // one 8-wave block per CU
+    long long g = std::min(cus, kMaxBlocks);  // one block per CU
     if (ub < g) g = ub;
     if (g >= 8) g &= ~7LL;
     return (unsigned)(g < 1 ? 1 : g);
@@ -1662,7 +2081,10 @@ hipError_t launch_ffn(const void* x_perm, const void* w_gate, const void* w_up, 
   g1.skpart = part;
   g1.tcnt = cnt + kTcntGU;
   g1.xcd_state = L.sk_ok ? xcd_state(s) : nullptr;
-  grouped_gemm_bf16_kernel<true><<<grid_for(I), kThreads, 0, s>>>(g1);
+  if (!sk && four_waves(true, M_cap, E_local, I))
+    grouped_gemm_bf16_kernel<true, 4><<<grid_for(I), 4 * kWave, 0, s>>>(g1);
+  else
+    grouped_gemm_bf16_kernel<true, 8><<<grid_for(I), 8 * kWave, 0, s>>>(g1);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   // A GEMM can split only if its K range holds two splits of kMinSplitChunks.
@@ -1683,7 +2105,10 @@ hipError_t launch_ffn(const void* x_perm, const void* w_gate, const void* w_up, 
   g2.skpart = part;
   g2.tcnt = cnt + kTcntDN;
   g2.xcd_state = g1.xcd_state;
-  grouped_gemm_bf16_kernel<false><<<grid_for(H), kThreads, 0, s>>>(g2);
+  if (!sk && four_waves(false, M_cap, E_local, H))
+    grouped_gemm_bf16_kernel<false, 4><<<grid_for(H), 4 * kWave, 0, s>>>(g2);
+  else
+    grouped_gemm_bf16_kernel<false, 8><<<grid_for(H), 8 * kWave, 0, s>>>(g2);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (split_dn && !sk)
@@ -1724,7 +2149,7 @@ size_t ffn_mx_ws_bytes(int M_cap, int E_local, int H, int I) {
   return ffn_mx_ws_layout(M_cap, E_local, H, I).bytes;
 }
 
-// One 8-wave block per CU, at most the tile bound (times the largest split
+// One block per CU, at most the tile bound (times the largest split
 // when split-K is possible), a multiple of 8.
 static unsigned mx_grid(int M_cap, int E_local, int N, bool split) {
   const long long ub = ((long long)(M_cap + kSmallM - 1) / kSmallM + E_local) * (N / 128) * (split ? kMaxSplit : 1);
@@ -1786,7 +2211,10 @@ static hipError_t gateup_mx(const uint8_t* xq, const uint32_t* xs, const uint8_t
   g.Bs1 = wus;
   g.Cs = hs;
   const bool split = sp.plan != nullptr && H / kMxChunk >= 2 * kMinSplitChunks;
-  grouped_gemm_mx_kernel<true><<<mx_grid(M_cap, E_local, I, split || g.sk), kThreads, 0, s>>>(g);
+  if (four_waves(true, M_cap, E_local, I))
+    grouped_gemm_mx_kernel<true, 4><<<mx_grid(M_cap, E_local, I, split || g.sk), 4 * kWave, 0, s>>>(g);
+  else
+    grouped_gemm_mx_kernel<true, 8><<<mx_grid(M_cap, E_local, I, split || g.sk), 8 * kWave, 0, s>>>(g);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || !split || sp.no_reduce) return e;
   split_reduce_mx_kernel<<<mx_reduce_grid(sp.plan_rows, I / 4), 256, 0, s>>>(sp.part, sp.plan, I, M_cap,
@@ -1811,7 +2239,10 @@ static hipError_t gemm_mx(const uint8_t* aq, const uint32_t* as, const uint8_t* 
   g.As = as;
   g.Bs0 = bs;
   const bool split = sp.plan != nullptr && K / kMxChunk >= 2 * kMinSplitChunks;
-  grouped_gemm_mx_kernel<false><<<mx_grid(M_cap, E_local, N, split || g.sk), kThreads, 0, s>>>(g);
+  if (four_waves(false, M_cap, E_local, N))
+    grouped_gemm_mx_kernel<false, 4><<<mx_grid(M_cap, E_local, N, split || g.sk), 4 * kWave, 0, s>>>(g);
+  else
+    grouped_gemm_mx_kernel<false, 8><<<mx_grid(M_cap, E_local, N, split || g.sk), 8 * kWave, 0, s>>>(g);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || !split || sp.no_reduce) return e;
   split_reduce_kernel<false><<<mx_reduce_grid(sp.plan_rows, N / 4), 256, 0, s>>>(sp.part, sp.plan, N,
@@ -1866,15 +2297,15 @@ hipError_t launch_ffn_mx(const uint8_t* xq, const uint32_t* xs, const uint8_t* w
 // itself loads all E router rows for every 64 tokens.
 // ---------------------------------------------------------------------------
 template <int BN>
-__global__ __launch_bounds__(kThreads) void router_logits_split_kernel(GemmArgs a, int S, float* __restrict__ part) {
-  __shared__ __align__(16) bf16_t smem[Stages<256, BN, false>::BYTES / 2];
+__global__ __launch_bounds__(512) void router_logits_split_kernel(GemmArgs a, int S, float* __restrict__ part) {
+  __shared__ __align__(16) bf16_t smem[Stages<256, BN, false, 8>::BYTES / 2];
   const int T = a.M_cap;
   const int m0 = (int)blockIdx.x * 256;
   const int m_end = min(m0 + 256, T);
   const int nK = a.K / kBK, sp = (int)blockIdx.y;
   const int kc0 = sp * nK / S, kc1 = (sp + 1) * nK / S;
   float* pbase = part + ((size_t)sp * T + m0) * BN;
-  gemm_tile<256, BN, 4, false, true>(a, smem, 0, m0, m_end, 0, kc0, kc1, pbase, 0, BN, 0);
+  gemm_tile<8, 256, BN, 4, false, true>(a, smem, 0, m0, m_end, 0, kc0, kc1, pbase, 0, BN, 0);
 }
 
 hipError_t launch_router_logits_split(const void* x, const void* wr, int T, int H, int E, int S, float* part,
@@ -1890,9 +2321,9 @@ hipError_t launch_router_logits_split(const void* x, const void* wr, int T, int 
   g.ldb = H;
   const dim3 grid((unsigned)((T + 255) / 256), (unsigned)S);
   if (E == 256)
-    router_logits_split_kernel<256><<<grid, kThreads, 0, s>>>(g, S, part);
+    router_logits_split_kernel<256><<<grid, 512, 0, s>>>(g, S, part);
   else if (E == 128)
-    router_logits_split_kernel<128><<<grid, kThreads, 0, s>>>(g, S, part);
+    router_logits_split_kernel<128><<<grid, 512, 0, s>>>(g, S, part);
   else
     return hipErrorInvalidValue;
   return hipGetLastError();

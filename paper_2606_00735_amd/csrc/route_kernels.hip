@@ -457,7 +457,8 @@ __global__ __launch_bounds__(512) void gate_topk_bf16_wide_kernel(
 #pragma unroll
   for (int j = 0; j < NI; ++j) acc[j] = f32x16_t{};
 
-  auto issue = [&](int kc, bool live, bf16_t* st) {
+  auto issue = [&](int kc, bool live, bf16_t* st, int part) {
+    if (part > 0) return;  // the chunk's loads all leave at once
     dma_rows<BT, 8, kGateBK>(xa, H, kc * kGateBK, a_rows, live, st, wave, lane);
     dma_rows<EP, 8, kGateBK>(wr, H, kc * kGateBK, E, live, st + BT * kGateBK, wave, lane);
   };
