@@ -17,19 +17,49 @@ namespace moe {
 constexpr int kPlaceThreads = 256;
 constexpr int kPlaceMaxE = 1024;  // experts per layer
 constexpr int kPlaceMaxG = 64;    // GPUs (one wave holds them)
+constexpr int kPlaceMaxNk = 64;   // knots of a latency model
 
 // f(n) of one GPU's model: knots (kn[k], kt[k]), k < nk, kn strictly
 // increasing and positive. f = 0 for n <= 0, kt[0] up to kn[0], linear
 // between knots, the last segment's slope beyond the last knot (with one
-// knot: kt[0] n / kn[0]).
+// knot: kt[0] n / kn[0]). The segment is found by bisection: a chain of at
+// most six dependent reads where a scan from the first knot takes nk.
 __device__ double latency_at(const double* kn, const double* kt, int nk, double n) {
   if (n <= 0.0) return 0.0;
   if (n <= kn[0]) return kt[0];
   if (nk == 1) return kt[0] * (n / kn[0]);
-  for (int k = 0; k + 1 < nk; ++k)
-    if (n <= kn[k + 1]) return kt[k] + (kt[k + 1] - kt[k]) * ((n - kn[k]) / (kn[k + 1] - kn[k]));
+  int lo = 1, hi = nk;  // the first knot k >= 1 with n <= kn[k], nk if there is none
+  while (lo < hi) {
+    const int mid = (lo + hi) >> 1;
+    if (n <= kn[mid]) hi = mid; else lo = mid + 1;
+  }
+  if (lo < nk) return kt[lo - 1] + (kt[lo] - kt[lo - 1]) * ((n - kn[lo - 1]) / (kn[lo] - kn[lo - 1]));
   const double lo_n = kn[nk - 2], hi_n = kn[nk - 1], lo_t = kt[nk - 2], hi_t = kt[nk - 1];
   return hi_t + (hi_t - lo_t) * ((n - hi_n) / (hi_n - lo_n));
+}
+
+// All G models in LDS (at most 64 x 64 knots): every block evaluates them many
+// times, each time a chain of dependent reads.
+struct Models {
+  double n[kPlaceMaxG * kPlaceMaxNk], t[kPlaceMaxG * kPlaceMaxNk];
+};
+__device__ __forceinline__ void load_models(Models& m, const double* knots_n, const double* knots_t, int G, int nk) {
+  for (int i = threadIdx.x; i < G * nk; i += blockDim.x) {
+    m.n[i] = knots_n[i];
+    m.t[i] = knots_t[i];
+  }
+}
+
+// Sum of w[e] over the experts with a[e] == g, in ascending e (both in LDS; all
+// lanes read the same words). Unrolled, so that only the adds are a chain.
+__device__ __forceinline__ double owned_sum(const double* w, const int* a, int E, int g) {
+  double n = 0.0;
+#pragma unroll 8
+  for (int e = 0; e < E; ++e) {
+    const double s = n + w[e];
+    n = a[e] == g ? s : n;
+  }
+  return n;
 }
 
 __device__ __forceinline__ double shfl_f64(double v, int src) {
@@ -37,18 +67,75 @@ __device__ __forceinline__ double shfl_f64(double v, int src) {
   return __builtin_bit_cast(double, make_int2(__shfl(p.x, src, kWave), __shfl(p.y, src, kWave)));
 }
 
-// (value, index) arg-max over one wave: larger value, then lower index.
-__device__ __forceinline__ void wave_argmax(double& v, int& i) {
+// (value, index) arg-max over lanes [0, 2^LOG): larger value, then lower index;
+// every one of those lanes gets the result (the others get that of their own
+// group). A strict order, so the shape of the reduction does not matter. The
+// exchanges within 16 lanes are DPP moves (a few cycles; a shuffle through LDS
+// takes about a hundred): lanes l ^ 1 and l ^ 2 of a quad, then the mirrored
+// lane of 8 and of 16, which holds the other half's result.
+template <int CTRL>
+__device__ __forceinline__ int dpp_i32(int v) {
+  return __builtin_amdgcn_update_dpp(v, v, CTRL, 0xf, 0xf, false);
+}
+__device__ __forceinline__ void take_better(double& v, int& i, double ov, int oi) {
+  const bool other = ov > v || (ov == v && oi < i);
+  v = other ? ov : v;
+  i = other ? oi : i;
+}
+template <int CTRL>
+__device__ __forceinline__ void argmax_dpp(double& v, int& i) {
+  const int2 p = __builtin_bit_cast(int2, v);
+  take_better(v, i, __builtin_bit_cast(double, make_int2(dpp_i32<CTRL>(p.x), dpp_i32<CTRL>(p.y))), dpp_i32<CTRL>(i));
+}
+template <int LOG>
+__device__ __forceinline__ void group_argmax(double& v, int& i) {
+  if constexpr (LOG >= 1) argmax_dpp<0xB1>(v, i);   // quad_perm 1, 0, 3, 2
+  if constexpr (LOG >= 2) argmax_dpp<0x4E>(v, i);   // quad_perm 2, 3, 0, 1
+  if constexpr (LOG >= 3) argmax_dpp<0x141>(v, i);  // row_half_mirror
+  if constexpr (LOG >= 4) argmax_dpp<0x140>(v, i);  // row_mirror
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
+  for (int off = 16; off < (1 << LOG); off <<= 1) {
     const int src = (threadIdx.x & 63) ^ off;
-    const double ov = shfl_f64(v, src);
-    const int oi = __shfl(i, src, kWave);
-    if (ov > v || (ov == v && oi < i)) {
-      v = ov;
-      i = oi;
-    }
+    take_better(v, i, shfl_f64(v, src), __shfl(i, src, kWave));
   }
+}
+
+__device__ __forceinline__ double readlane_f64(double v, int lane) {
+  const int2 p = __builtin_bit_cast(int2, v);
+  return __builtin_bit_cast(double, make_int2(__builtin_amdgcn_readlane(p.x, lane), __builtin_amdgcn_readlane(p.y, lane)));
+}
+
+// The greedy of one wave over experts in the sorted order (key: load, id:
+// expert): lane g holds tau_g, its load n and its expert count; G <= 2^LOG.
+// 64 experts at a time sit in the wave's registers and are broadcast from
+// there, so a step is the arg-max and the winner's update.
+template <int LOG>
+__device__ __forceinline__ double greedy_assign(const double* key, const int* id, int E, int G, int cap, double tau,
+                                                int* s_assign) {
+  const int g = threadIdx.x;
+  double n = 0.0;
+  int cnt = 0;
+  for (int r0 = 0; r0 < E; r0 += kWave) {
+    const int mine = min(r0 + g, E - 1);
+    const double my_key = key[mine];
+    const int my_id = id[mine];
+    int my_gpu = 0;
+    const int m = min(kWave, E - r0);
+    for (int r = 0; r < m; ++r) {
+      double gap = (g < G && (cap == 0 || cnt < cap)) ? tau - n : -__builtin_inf();
+      int best = g < G ? g : 0x7fffffff;
+      group_argmax<LOG>(gap, best);
+      best = __builtin_amdgcn_readfirstlane(best);
+      const double w = readlane_f64(my_key, r);
+      if (g == best) {
+        n += w;
+        ++cnt;
+      }
+      if (g == r) my_gpu = best;
+    }
+    if (g < m && my_id < E) s_assign[my_id] = my_gpu;  // (unordered loads could bring a padding id here)
+  }
+  return n;
 }
 
 // ---------------------------------------------------------------------------
@@ -60,13 +147,16 @@ __global__ __launch_bounds__(kPlaceThreads) void place_greedy_kernel(const doubl
                                                                      int nk, int cap, int32_t* __restrict__ assign,
                                                                      double* __restrict__ loads,
                                                                      double* __restrict__ targets) {
+  __shared__ Models s_m;
   __shared__ double s_w[kPlaceMaxE];
   __shared__ double s_key[kPlaceMaxE];  // sort keys: load, descending
   __shared__ int s_id[kPlaceMaxE];      // expert ids, ascending among equal loads
+  __shared__ int s_assign[kPlaceMaxE];
   __shared__ double s_speed[kPlaceMaxG];
   __shared__ double s_N, s_S;
   const int l = blockIdx.x, tid = threadIdx.x;
   const double* w = W + (size_t)l * E;
+  load_models(s_m, knots_n, knots_t, G, nk);
 
   int P = 1;
   while (P < E) P <<= 1;
@@ -75,6 +165,7 @@ __global__ __launch_bounds__(kPlaceThreads) void place_greedy_kernel(const doubl
       s_w[i] = w[i];
       s_key[i] = w[i];
       s_id[i] = i;
+      s_assign[i] = 0;
     } else {
       s_key[i] = -__builtin_inf();
       s_id[i] = 0x7fffffff;
@@ -83,15 +174,14 @@ __global__ __launch_bounds__(kPlaceThreads) void place_greedy_kernel(const doubl
   __syncthreads();
   if (tid == 0) {  // N = sum_e w_e in ascending e
     double N = 0.0;
+#pragma unroll 16
     for (int e = 0; e < E; ++e) N += s_w[e];
     s_N = N;
   }
   __syncthreads();
   const double N = s_N;
   if (tid < G) {
-    const double* kn = knots_n + (size_t)tid * nk;
-    const double* kt = knots_t + (size_t)tid * nk;
-    s_speed[tid] = N > 0.0 ? 1.0 / latency_at(kn, kt, nk, N / E) : 1.0;
+    s_speed[tid] = N > 0.0 ? 1.0 / latency_at(s_m.n + tid * nk, s_m.t + tid * nk, nk, N / E) : 1.0;
   }
   __syncthreads();
   if (tid == 0) {
@@ -120,27 +210,23 @@ __global__ __launch_bounds__(kPlaceThreads) void place_greedy_kernel(const doubl
       }
     }
   __syncthreads();
-  if (tid >= kWave) return;
-  // greedy: lane g holds tau_g, n_g and its expert count
-  const int g = tid;
-  const double tau = g < G ? N * s_speed[g] / s_S : 0.0;
-  double n = 0.0;
-  int cnt = 0;
-  for (int r = 0; r < E; ++r) {
-    const int e = s_id[r];
-    double gap = (g < G && (cap == 0 || cnt < cap)) ? tau - n : -__builtin_inf();
-    int best = g < G ? g : 0x7fffffff;
-    wave_argmax(gap, best);
-    if (g == best) {
-      n += s_w[e];
-      ++cnt;
+  if (tid < kWave) {
+    const int g = tid;
+    const double tau = g < G ? N * s_speed[g] / s_S : 0.0;
+    double n;
+    if (G <= 8)
+      n = greedy_assign<3>(s_key, s_id, E, G, cap, tau, s_assign);
+    else if (G <= 16)
+      n = greedy_assign<4>(s_key, s_id, E, G, cap, tau, s_assign);
+    else
+      n = greedy_assign<6>(s_key, s_id, E, G, cap, tau, s_assign);
+    if (g < G) {
+      if (loads) loads[(size_t)l * G + g] = n;
+      if (targets) targets[(size_t)l * G + g] = tau;
     }
-    if (g == 0) assign[(size_t)l * E + e] = best;
   }
-  if (g < G) {
-    if (loads) loads[(size_t)l * G + g] = n;
-    if (targets) targets[(size_t)l * G + g] = tau;
-  }
+  __syncthreads();
+  for (int e = tid; e < E; e += kPlaceThreads) assign[(size_t)l * E + e] = s_assign[e];
 }
 
 // ---------------------------------------------------------------------------
@@ -149,6 +235,7 @@ __global__ __launch_bounds__(kPlaceThreads) void place_greedy_kernel(const doubl
 __global__ __launch_bounds__(kPlaceThreads) void place_incremental_kernel(
     const double* __restrict__ W, int E, const double* __restrict__ knots_n, const double* __restrict__ knots_t,
     int G, int nk, double eps, int max_swaps, int32_t* __restrict__ assign, int32_t* __restrict__ n_swaps) {
+  __shared__ Models s_m;
   __shared__ double s_w[kPlaceMaxE];
   __shared__ int s_a[kPlaceMaxE];
   __shared__ int s_hi_list[kPlaceMaxE], s_lo_list[kPlaceMaxE];
@@ -159,19 +246,17 @@ __global__ __launch_bounds__(kPlaceThreads) void place_incremental_kernel(
   const int l = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const double* w = W + (size_t)l * E;
   int32_t* a = assign + (size_t)l * E;
+  load_models(s_m, knots_n, knots_t, G, nk);
   for (int e = tid; e < E; e += kPlaceThreads) {
     s_w[e] = w[e];
     const int g = a[e];
     s_a[e] = (g >= 0 && g < G) ? g : 0;  // placements out of range are read as GPU 0
   }
   __syncthreads();
-  if (tid == 0) {  // n_g in ascending expert id
-    for (int g = 0; g < G; ++g) s_n[g] = 0.0;
-    for (int e = 0; e < E; ++e) s_n[s_a[e]] += s_w[e];
-  }
+  if (tid < G) s_n[tid] = owned_sum(s_w, s_a, E, tid);  // n_g in ascending expert id
   __syncthreads();
   auto lat_of = [&](int g, double n) {
-    return latency_at(knots_n + (size_t)g * nk, knots_t + (size_t)g * nk, nk, n);
+    return latency_at(s_m.n + g * nk, s_m.t + g * nk, nk, n);
   };
   int swaps = 0;
   for (;;) {
@@ -277,28 +362,38 @@ __global__ __launch_bounds__(kPlaceThreads) void place_incremental_kernel(
 // n_g = sum_{e in S_g} w_e (ascending e), f_g(n_g), and the grouped reading
 // sum_{e in S_g} f_g(w_e). The layer latency is the maximum over GPUs.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kWave) void placement_cost_kernel(const double* __restrict__ W,
-                                                               const int32_t* __restrict__ assign, int E,
-                                                               const double* __restrict__ knots_n,
-                                                               const double* __restrict__ knots_t, int G, int nk,
-                                                               double* __restrict__ loads,
-                                                               double* __restrict__ lat,
-                                                               double* __restrict__ lat_grouped) {
-  const int l = blockIdx.x, g = threadIdx.x;
+__global__ __launch_bounds__(kPlaceThreads) void placement_cost_kernel(const double* __restrict__ W,
+                                                                       const int32_t* __restrict__ assign, int E,
+                                                                       const double* __restrict__ knots_n,
+                                                                       const double* __restrict__ knots_t, int G,
+                                                                       int nk, double* __restrict__ loads,
+                                                                       double* __restrict__ lat,
+                                                                       double* __restrict__ lat_grouped) {
+  __shared__ Models s_m;
+  __shared__ double s_w[kPlaceMaxE], s_f[kPlaceMaxE];
+  __shared__ int s_a[kPlaceMaxE];
+  const int l = blockIdx.x, tid = threadIdx.x;
+  load_models(s_m, knots_n, knots_t, G, nk);
+  for (int e = tid; e < E; e += kPlaceThreads) {
+    s_w[e] = W[(size_t)l * E + e];
+    s_a[e] = assign[(size_t)l * E + e];
+  }
+  __syncthreads();
+  // every expert's own latency side by side, then two sums per GPU
+  for (int e = tid; e < E; e += kPlaceThreads) {
+    const int g = s_a[e];
+    if (g >= 0 && g < G) s_f[e] = latency_at(s_m.n + g * nk, s_m.t + g * nk, nk, s_w[e]);
+  }
+  __syncthreads();
+  const int g = tid & (kPlaceMaxG - 1), which = tid / kPlaceMaxG;  // one wave per sum
   if (g >= G) return;
-  const double* w = W + (size_t)l * E;
-  const int32_t* a = assign + (size_t)l * E;
-  const double* kn = knots_n + (size_t)g * nk;
-  const double* kt = knots_t + (size_t)g * nk;
-  double n = 0.0, grouped = 0.0;
-  for (int e = 0; e < E; ++e)
-    if (a[e] == g) {
-      n += w[e];
-      grouped += latency_at(kn, kt, nk, w[e]);
-    }
-  if (loads) loads[(size_t)l * G + g] = n;
-  lat[(size_t)l * G + g] = latency_at(kn, kt, nk, n);
-  if (lat_grouped) lat_grouped[(size_t)l * G + g] = grouped;
+  if (which == 0) {
+    const double n = owned_sum(s_w, s_a, E, g);
+    if (loads) loads[(size_t)l * G + g] = n;
+    lat[(size_t)l * G + g] = latency_at(s_m.n + g * nk, s_m.t + g * nk, nk, n);
+  } else if (which == 1 && lat_grouped) {
+    lat_grouped[(size_t)l * G + g] = owned_sum(s_f, s_a, E, g);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -313,29 +408,60 @@ __global__ void window_push_kernel(const int32_t* __restrict__ counts, int32_t* 
   ring_slot[i] = c;
 }
 
-// One block: thread t handles layers t, t + 256, ...; the trigger is the OR
-// of d > delta over all layers, written by thread 0 (no atomics, no memset).
-__global__ __launch_bounds__(256) void drift_distance_kernel(const double* __restrict__ w_cur,
-                                                             const double* __restrict__ w_ref, int L, int E,
-                                                             double delta, double* __restrict__ d,
-                                                             int32_t* __restrict__ trigger) {
+// One block, so that the trigger (the OR of d > delta over all layers, written
+// by thread 0) needs no atomics and no memset. Each of its 16 waves takes
+// kDriftLayers layers at a time: the lanes read 64 experts of each, coalesced,
+// and put the products u v, u u and v v into LDS; one lane per (layer, sum) then
+// adds them in ascending expert id. A lane of its own per layer read its
+// vectors alone, two dependent loads an expert.
+constexpr int kDriftThreads = 1024;
+constexpr int kDriftLayers = 4;
+__global__ __launch_bounds__(kDriftThreads) void drift_distance_kernel(const double* __restrict__ w_cur,
+                                                                       const double* __restrict__ w_ref, int L, int E,
+                                                                       double delta, double* __restrict__ d,
+                                                                       int32_t* __restrict__ trigger) {
+  constexpr int NW = kDriftThreads / kWave, NS = 3 * kDriftLayers, LD = kWave + 1;  // rows off a bank
+  __shared__ double s_p[NW][NS * LD];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  double* p = s_p[wave];
   bool over = false;
-  for (int l = threadIdx.x; l < L; l += 256) {
-    const double* u = w_cur + (size_t)l * E;
-    const double* v = w_ref + (size_t)l * E;
-    double dot = 0.0, na = 0.0, nb = 0.0;
-    for (int e = 0; e < E; ++e) {
-      dot += u[e] * v[e];
-      na += u[e] * u[e];
-      nb += v[e] * v[e];
+  for (int l0 = 0; l0 < L; l0 += NW * kDriftLayers) {
+    const int lw = l0 + wave * kDriftLayers;  // this wave's first layer
+    double sum = 0.0;                         // lane q < NS: sum q % 3 of layer lw + q / 3
+    for (int e0 = 0; e0 < E; e0 += kWave) {
+      const int e = e0 + lane;
+      double u[kDriftLayers], v[kDriftLayers];
+#pragma unroll
+      for (int q = 0; q < kDriftLayers; ++q) {
+        const bool in = lw + q < L && e < E;
+        u[q] = in ? w_cur[(size_t)(lw + q) * E + e] : 0.0;
+        v[q] = in ? w_ref[(size_t)(lw + q) * E + e] : 0.0;
+      }
+      __syncthreads();  // the sums below are done with the products before
+#pragma unroll
+      for (int q = 0; q < kDriftLayers; ++q) {
+        p[(3 * q) * LD + lane] = u[q] * v[q];
+        p[(3 * q + 1) * LD + lane] = u[q] * u[q];
+        p[(3 * q + 2) * LD + lane] = v[q] * v[q];
+      }
+      __syncthreads();
+      const int m = min(kWave, E - e0);
+      if (lane < NS) {
+#pragma unroll 16
+        for (int i = 0; i < m; ++i) sum += p[lane * LD + i];
+      }
     }
-    double dist;
-    if (na == 0.0 || nb == 0.0)
-      dist = (na == nb) ? 0.0 : 1.0;
-    else
-      dist = 1.0 - dot / (__builtin_sqrt(na) * __builtin_sqrt(nb));
-    d[l] = dist;
-    over = over || dist > delta;
+    const double dot = shfl_f64(sum, (3 * lane) & 63), na = shfl_f64(sum, (3 * lane + 1) & 63),
+                 nb = shfl_f64(sum, (3 * lane + 2) & 63);
+    if (lane < kDriftLayers && lw + lane < L) {
+      double dist;
+      if (na == 0.0 || nb == 0.0)
+        dist = (na == nb) ? 0.0 : 1.0;
+      else
+        dist = 1.0 - dot / (__builtin_sqrt(na) * __builtin_sqrt(nb));
+      d[lw + lane] = dist;
+      over = over || dist > delta;
+    }
   }
   const int any = __syncthreads_or(over ? 1 : 0);
   if (threadIdx.x == 0 && trigger) *trigger = any ? 1 : 0;
@@ -363,7 +489,7 @@ hipError_t launch_placement_cost(const double* W, const int32_t* assign, int L, 
                                  const double* kt, int G, int nk, double* loads, double* lat, double* lat_grouped,
                                  hipStream_t s) {
   if (L == 0) return hipSuccess;
-  placement_cost_kernel<<<L, kWave, 0, s>>>(W, assign, E, kn, kt, G, nk, loads, lat, lat_grouped);
+  placement_cost_kernel<<<L, kPlaceThreads, 0, s>>>(W, assign, E, kn, kt, G, nk, loads, lat, lat_grouped);
   return hipGetLastError();
 }
 
@@ -377,7 +503,7 @@ hipError_t launch_window_push(const int32_t* counts, int32_t* ring, double* sums
 
 hipError_t launch_drift_distance(const double* w_cur, const double* w_ref, int L, int E, double delta, double* d,
                                  int32_t* trigger, hipStream_t s) {
-  drift_distance_kernel<<<1, 256, 0, s>>>(w_cur, w_ref, L, E, delta, d, trigger);
+  drift_distance_kernel<<<1, kDriftThreads, 0, s>>>(w_cur, w_ref, L, E, delta, d, trigger);
   return hipGetLastError();
 }
 
