@@ -63,7 +63,8 @@ def _np(t):
 def test_bf16(H, I, rows):
     print("CASE large tile bf16", H, I, rows, flush=True)
     x, wg, wu, wd, off = _inputs(H, I, rows, 1)
-    M, cap = x.shape[0], max(4096 * len(rows), 2**25 // H)
+    M = x.shape[0]
+    cap = max(M, 4096 * len(rows), 2**25 // H)
     xb = torch.zeros((cap, H), dtype=x.dtype, device="cuda")
     xb[:M] = x
     y8, ws8 = moe.moe_grouped_swiglu_ffn(x, wg, wu, wd, off)
@@ -90,7 +91,8 @@ def test_mx(H, I, rows):
     """H = 384, 896 and I = 384, 640: an odd number of 128-element chunks."""
     print("CASE large tile mx", H, I, rows, flush=True)
     x, wg, wu, wd, off = _inputs(H, I, rows, 3)
-    M, cap = x.shape[0], max(4096 * len(rows), 2**25 // H)
+    M = x.shape[0]
+    cap = max(M, 4096 * len(rows), 2**25 // H)
     xb = torch.zeros((cap, H), dtype=x.dtype, device="cuda")
     xb[:M] = x
     w = [moe.moe_mx_quantize(t) for t in (wg, wu, wd)]
