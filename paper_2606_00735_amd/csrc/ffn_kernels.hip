@@ -160,34 +160,52 @@ __device__ __forceinline__ f32x4_t ld_coh4(const float* p) {
 // decode_schedule) and the stores have completed on return; coh: stored with
 // st_coh4, for a block on another XCD, else with ordinary stores, which a
 // block on the same XCD reads from their shared L2.
+// Through LDS as in store_block (32 rows of one matrix at a time: a direct
+// store touches 32 rows with 32 bytes each).
 template <int MI, int NI, int NB, int WM, int WN, bool COH = false>
-__device__ __forceinline__ void split_epilogue(const f32x16_t (&acc)[NB][MI][NI], int m0, int m_end, int col0,
-                                               int ld, int wm, int wn, int lane, float* pbase, size_t pstride,
-                                               bool coh) {
+__device__ __forceinline__ void split_epilogue(const f32x16_t (&acc)[NB][MI][NI], bf16_t* smem, int m0, int m_end,
+                                               int col0, int ld, int wm, int wn, int wave, int lane, float* pbase,
+                                               size_t pstride, bool coh) {
+  constexpr int RB = WN * 4, PP = RB / 16;  // bytes and 16-byte pieces of a row
+  static_assert(RB == 512 || RB == 256 || RB == 128, "row bytes");
+  auto key = [](int r) { return PP >= 16 ? (r & 15) : ((r >> 1) & 7); };  // see store_block
+  char* blk = reinterpret_cast<char*>(smem) + wave * (32 * RB);
+  asm volatile("" : "+v"(lane));  // see store_block
+  const int r32 = lane & 31, hi = lane >> 5;
 #pragma unroll
   for (int i = 0; i < MI; ++i) {
-    const int r = wm * WM + i * 32 + (lane & 31);  // row within the tile
-    if (m0 + r < m_end) {
+    const int r0 = wm * WM + i * 32;  // first row within the tile
+    if (m0 + r0 < m_end) {
 #pragma unroll
       for (int b = 0; b < NB; ++b) {
-        float* prow = pbase + b * pstride + (size_t)r * ld + col0 + wn * WN + 4 * (lane >> 5);
 #pragma unroll
         for (int j = 0; j < NI; ++j)
 #pragma unroll
-          for (int g = 0; g < 4; ++g) {
-            float* p = prow + j * 32 + 8 * g;
-            if (COH && coh) {
-              st_coh4(p, f32x4_t{acc[b][i][j][4 * g], acc[b][i][j][4 * g + 1], acc[b][i][j][4 * g + 2],
-                                 acc[b][i][j][4 * g + 3]});
-            } else {
-              *reinterpret_cast<float4*>(p) = make_float4(acc[b][i][j][4 * g], acc[b][i][j][4 * g + 1],
-                                                          acc[b][i][j][4 * g + 2], acc[b][i][j][4 * g + 3]);
-            }
+          for (int g = 0; g < 4; ++g)
+            *reinterpret_cast<float4*>(blk + r32 * RB + (((j * 8 + 2 * g + hi) ^ key(r32)) * 16)) =
+                make_float4(acc[b][i][j][4 * g], acc[b][i][j][4 * g + 1], acc[b][i][j][4 * g + 2],
+                            acc[b][i][j][4 * g + 3]);
+        __builtin_amdgcn_sched_barrier(0);
+        float* out = pbase + b * pstride + (size_t)r0 * ld + col0 + wn * WN;
+#pragma unroll
+        for (int it = 0; it < 32 * PP / 64; ++it) {
+          const int row = (it * 64 + lane) / PP, p = lane % PP;
+          const f32x4_t v = *reinterpret_cast<const f32x4_t*>(blk + row * RB + ((p ^ key(row)) * 16));
+          if (m0 + r0 + row < m_end) {
+            float* q = out + (size_t)row * ld + p * 4;
+            if (COH && coh)
+              st_coh4(q, v);
+            else
+              *reinterpret_cast<f32x4_t*>(q) = v;
           }
+        }
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
   }
   if (COH) wait_vmcnt<0>();
+  wait_lgkmcnt0();
+  lds_barrier();
 }
 
 // A wave's ROWS x COLS block of a tile's output, from the MFMA register layout
@@ -217,6 +235,7 @@ __device__ __forceinline__ void store_block(bf16_t* smem, void* C, int N, int ro
   // 32 rows at a time, in a fixed order: the register budget has no room for more
 #pragma unroll
   for (int i = 0; i < ROWS / 32; ++i) {
+    if (row0 + i * 32 >= m_end) break;
     char* blk = lds + i * 32 * RB;
 #pragma unroll
     for (int j = 0; j < COLS / 32; ++j)
@@ -368,7 +387,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, bf16_t* smem, int e
   // owns 4 consecutive columns per group g = v / 4 and stores them as one
   // 8-byte write (or, for a split-K partial, one 16-byte fp32 write).
   if (SPLIT) {
-    split_epilogue<MI, NI, NB, WM, WN, COH>(acc, m0, m_end, pcol0, pld, wm, wn, lane, pbase, pstride, coh);
+    split_epilogue<MI, NI, NB, WM, WN, COH>(acc, smem, m0, m_end, pcol0, pld, wm, wn, wave, lane, pbase, pstride,
+                                            coh);
     return;
   }
   store_block<WM, WN, 2>(smem, a.C, N, m0 + wm * WM, m_end, n0 + wn * WN, wave, lane, [&](int i, int j, int g) {
@@ -607,7 +627,8 @@ __device__ __forceinline__ void gemm_tile_mx(const GemmArgs& a, bf16_t* smem, in
   pipeline_xk<St::NS, St::LOADS, KS, true>(kc1 - kc0, smem, St::STAGE / 2, issue, read, mma, mix);
 
   if (SPLIT) {
-    split_epilogue<MI, NI, NB, WM, WN, COH>(acc, m0, m_end, pcol0, pld, wm, wn, lane, pbase, pstride, coh);
+    split_epilogue<MI, NI, NB, WM, WN, COH>(acc, smem, m0, m_end, pcol0, pld, wm, wn, wave, lane, pbase, pstride,
+                                            coh);
     return;
   }
 
@@ -897,26 +918,13 @@ __device__ __forceinline__ void big_tile(const GemmArgs& a, bf16_t* smem, int e,
   // the 32 x 32 block for token row l % 32 (see gemm_tile); row block i of the
   // wave's four is (A half i / 2, block i % 2).
   if (pbase != nullptr) {
+    // B half b is a matrix of its own (dual) or 64 of the wave's 128 columns
 #pragma unroll
     for (int h = 0; h < 2; ++h)
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const int r = wm * 128 + h * 64 + i * 32 + r32;  // row within the tile
-        if (m0 + r < m_end) {
-#pragma unroll
-          for (int b = 0; b < 2; ++b) {
-            float* p = pbase + (DUAL ? b * pstride : 0) + (size_t)r * pld + pcol0 +
-                       (DUAL ? wn * 64 : wn * 128 + b * 64) + 4 * hi;
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-#pragma unroll
-              for (int g = 0; g < 4; ++g)
-                *reinterpret_cast<float4*>(p + j * 32 + 8 * g) =
-                    make_float4(acc[h][b][i][j][4 * g], acc[h][b][i][j][4 * g + 1], acc[h][b][i][j][4 * g + 2],
-                                acc[h][b][i][j][4 * g + 3]);
-          }
-        }
-      }
+      split_epilogue<2, 2, 2, 64, 64>(acc[h], smem, m0 + wm * 128 + h * 64, m_end, pcol0, pld, 0, 0, wave,
+                                      lane,
+                                      pbase + (size_t)(wm * 128 + h * 64) * pld + (DUAL ? wn * 64 : wn * 128),
+                                      DUAL ? pstride : (size_t)64, false);
     return;
   }
   if constexpr (DUAL && MX) {
