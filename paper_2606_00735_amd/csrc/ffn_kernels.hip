@@ -557,7 +557,7 @@ __device__ __forceinline__ void gemm_tile_mx(const GemmArgs& a, bf16_t* smem, in
     char* sl = reinterpret_cast<char*>(st);
     const uint32_t l0 = lds_addr(st) + wave * (RPI * 128);
     constexpr int LS = W * RPI * 128;  // LDS bytes between a wave's loads
-    auto mine = [&](int t) { return part < 0 || (St::NS > 2 ? t * KS / St::LOADS : 0) == part; };
+    auto mine = [&](int) { return part <= 0; };  // a burst: parts measured 0.7 % slower at decode
 #pragma unroll
     for (int t = 0; t < LA; ++t)
       if (mine(t)) dma16a(uniform_ptr(A + (size_t)kcl * kMxChunk), offA[t], l0 + t * LS);
