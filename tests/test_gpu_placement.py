@@ -169,3 +169,41 @@ def test_placement_cost_matches_oracle():
         assert np.array_equal(lat[l], [P.latency(kn[g], kt[g], rn[g]) for g in range(G)])
         assert lat[l].max() == P.layer_latency(A[l], W[l], kn, kt)
         assert latg[l].max() == P.layer_latency(A[l], W[l], kn, kt, grouped=True)
+
+
+EDGES = [
+    # layers around a round of the drift kernel (64), experts around a wave,
+    # GPUs around the arg-max groups (8, 16), model sizes 1, 2 and the largest
+    (1, 1, 1, 1), (64, 63, 8, 2), (65, 65, 9, 3), (130, 64, 16, 64), (3, 1000, 17, 5), (2, 1024, 64, 64),
+]
+
+
+@pytest.mark.parametrize("Lyr,E,G,nk", EDGES, ids=[f"L{a}-E{b}-G{c}-nk{d}" for a, b, c, d in EDGES])
+def test_kernel_edges_match_oracle(Lyr, E, G, nk):
+    banner("placement edges", Lyr, E, G, nk)
+    W, ref = loads(Lyr, E, seed=E, integer=False), loads(Lyr, E, seed=E + 1, integer=False)
+    rng = np.random.default_rng(nk)
+    kn = np.cumsum(rng.uniform(1.0, 4.0, (G, nk)), axis=1) * W.sum(1).mean() / (2 * G * nk)
+    kt = 20.0 + np.cumsum(rng.uniform(0.0, 3.0, (G, nk)), axis=1)
+    W[0, 0] = kn[0, nk // 2]  # a load on a knot
+    a, n, tau = moe.moe_place_greedy(dev(W), dev(kn), dev(kt))
+    c = moe.moe_placement_cost(dev(W), a, dev(kn), dev(kt))
+    d, trig = moe.moe_drift_distance(dev(W), dev(ref), delta=0.05)
+    u = dev(rng.integers(0, G, (Lyr, E)), torch.int32)
+    start = u.cpu().numpy().copy()
+    swaps = moe.moe_place_incremental(dev(W), dev(kn), dev(kt), u, eps=0.02, max_swaps=3)
+    torch.cuda.synchronize()
+    a, n, tau, u, swaps = (t.cpu().numpy() for t in (a, n, tau, u, swaps))
+    c, d = [t.cpu().numpy() for t in c], d.cpu().numpy()
+    for l in sorted({0, 1, Lyr // 2, Lyr - 1} & set(range(Lyr))):
+        ra, rn, rt = P.greedy_placement(W[l], kn, kt)
+        assert np.array_equal(a[l], ra) and np.array_equal(n[l], rn) and np.array_equal(tau[l], rt), f"layer {l}"
+        cn = P.gpu_loads(ra, W[l], G)
+        assert np.array_equal(c[0][l], cn), f"layer {l}"
+        assert np.array_equal(c[1][l], [P.latency(kn[g], kt[g], cn[g]) for g in range(G)]), f"layer {l}"
+        assert c[2][l].max() == P.layer_latency(ra, W[l], kn, kt, grouped=True), f"layer {l}"
+        ru, rs = P.incremental_update(start[l], W[l], kn, kt, eps=0.02, max_swaps=3)
+        assert np.array_equal(u[l], ru) and swaps[l] == rs, f"layer {l}"
+    for l in range(Lyr):
+        assert d[l] == P.cosine_distance(W[l], ref[l]), f"layer {l}"
+    assert int(trig.item()) == int(d.max() > 0.05)
