@@ -111,8 +111,12 @@ def _check(fn, status):
         raise MoeError(fn, status, text)
 
 
+# A layer is seven to nine launches of a few microseconds each at decode sizes,
+# so what the host does between two of them shows: pointers go to ctypes as
+# plain integers (its argument types convert them), and the stream's handle is
+# taken without building a torch Stream object around it.
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _dev(t, name, dtype=None):
@@ -124,7 +128,7 @@ def _dev(t, name, dtype=None):
         raise ValueError(f"{name} must be contiguous")
     if dtype is not None and t.dtype != dtype:
         raise ValueError(f"{name} must be {dtype}, got {t.dtype}")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _wrows(t, name, dtype):
@@ -138,12 +142,13 @@ def _wrows(t, name, dtype):
     if t.dtype != dtype:
         raise ValueError(f"{name} must be {dtype}, got {t.dtype}")
     B, R, K = t.shape
-    if t.numel() == 0:  # no experts (or empty matrices): nothing is read
-        return ctypes.c_void_p(t.data_ptr()), K
-    ld = t.stride(1) if R > 1 else K
-    if t.stride(2) != 1 or ld < K or (B > 1 and t.stride(0) != R * ld):
+    if B == 0 or R == 0 or K == 0:  # no experts (or empty matrices): nothing is read
+        return t.data_ptr(), K
+    sb, sr, sk = t.stride()
+    ld = sr if R > 1 else K
+    if sk != 1 or ld < K or (B > 1 and sb != R * ld):
         raise ValueError(f"{name} must be [B, R, K] with unit element stride and rows {ld} apart")
-    return ctypes.c_void_p(t.data_ptr()), ld
+    return t.data_ptr(), ld
 
 
 def _dtype_code(t):
@@ -156,11 +161,11 @@ def _dtype_code(t):
 
 def _host_map(expert_map):
     a = np.ascontiguousarray(np.asarray(expert_map, dtype=np.int32))
-    return a, a.ctypes.data_as(ctypes.c_void_p)
+    return a, a.__array_interface__["data"][0]
 
 
 def _ptr_or_null(t, name, dtype=None):
-    return ctypes.c_void_p(None) if t is None else _dev(t, name, dtype)
+    return None if t is None else _dev(t, name, dtype)
 
 
 # ---------------------------------------------------------------------------
@@ -191,7 +196,7 @@ def moe_gate_topk(x, w_router, bias, k, logits=False, ids=None, weights=None, ws
     weights = torch.empty((T, k), dtype=torch.float32, device=dev) if weights is None else weights
     lg = torch.empty((T, E), dtype=torch.float32, device=dev) if logits is True else (
         logits if isinstance(logits, torch.Tensor) else None)
-    pws, n = ctypes.c_void_p(None), None
+    pws, n = None, None
     if use_ws:
         need = gate_ws_bytes(T, H, E, x.dtype)
         if need > 0:
@@ -222,7 +227,7 @@ def moe_expert_histogram_scan(ids, E, expert_map, ws=None, counts=None, offsets=
     emap, emap_p = _host_map(expert_map)
     if emap.shape != (E,):
         raise ValueError("expert_map must have E entries")
-    E_local = int((emap >= 0).sum())
+    E_local = int(np.count_nonzero(emap >= 0))
     need = hist_ws_bytes(T, k, E, E_local)
     dev = ids.device
     if ws is None:
@@ -246,7 +251,7 @@ def moe_permute(x, ids, expert_map, ws, M_cap=None, x_perm=None, perm_src=None, 
     k = ids.shape[1]
     emap, emap_p = _host_map(expert_map)
     E = emap.shape[0]
-    E_local = int((emap >= 0).sum())
+    E_local = int(np.count_nonzero(emap >= 0))
     M_cap = T * k if M_cap is None else M_cap
     dev = x.device
     if not gather:
