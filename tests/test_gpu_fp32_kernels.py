@@ -1,0 +1,67 @@
+"""The fp32 FFN and router kernels where their blocks end: columns around 32 a
+block, rows of fewer pieces than lanes, experts looked up 64 at a time, rows
+past the last expert, router rows that are no multiple of its 32-element step.
+
+Bound of an fp32 dot product of K terms in any order: (K + 2) 2^-24 sum |a b|."""
+import pytest
+import torch
+
+import paper_2606_00735_amd as moe
+
+pytestmark = pytest.mark.gpu
+EPS = 2.0 ** -24
+
+FFN = [
+    # H, I, rows per expert
+    (4, 4, [1]),
+    (28, 36, [3, 0, 5]),
+    (128, 256, [16] * 8),
+    (132, 68, [0] * 63 + [2, 1] + [0] * 40 + [7]),  # experts 63, 64 and 105
+    (1028, 100, [0, 9, 0]),
+]
+
+
+@pytest.mark.parametrize("H,I,rows", FFN, ids=[f"H{h}-I{i}-E{len(r)}" for h, i, r in FFN])
+def test_ffn(H, I, rows):
+    print("CASE fp32 ffn", H, I, rows, flush=True)
+    g = torch.Generator(device="cuda").manual_seed(H + I)
+    E, M = len(rows), sum(rows)
+    cap = M + 5  # rows past the last expert are left alone
+
+    def rnd(*s):
+        return torch.randn(*s, generator=g, device="cuda") * s[-1] ** -0.5
+
+    x, wg, wu, wd = rnd(cap, H), rnd(E, I, H), rnd(E, I, H), rnd(E, H, I)
+    off = torch.tensor([0] + list(torch.tensor(rows).cumsum(0)), dtype=torch.int32, device="cuda")
+    y = torch.full((cap, H), float("nan"), device="cuda")
+    y, ws = moe.moe_grouped_swiglu_ffn(x, wg, wu, wd, off, y_perm=y)
+    torch.cuda.synchronize()
+    h = moe.ffn_hidden(ws, cap, I, x.dtype)
+    assert bool(y[M:].isnan().all())
+    r0 = 0
+    for e, n in enumerate(rows):
+        if n == 0:
+            continue
+        xe, he = x[r0:r0 + n].double(), h[r0:r0 + n].double()
+        a, u = xe @ wg[e].double().t(), xe @ wu[e].double().t()
+        da, du = ((H + 2) * EPS * (xe.abs() @ w[e].double().abs().t()) for w in (wg, wu))
+        # |silu'| <= 1.1 and |silu(a)| <= |a|; expf, division and products: 8 roundings
+        ref = a * torch.sigmoid(a) * u
+        assert bool(((he - ref).abs() <= 1.1 * da * (u.abs() + du) + a.abs() * du + 8 * EPS * ref.abs()).all()), e
+        dy = (I + 2) * EPS * (he.abs() @ wd[e].double().abs().t())
+        assert bool(((y[r0:r0 + n].double() - he @ wd[e].double().t()).abs() <= dy).all()), e
+        r0 += n
+
+
+@pytest.mark.parametrize("T,H,E,k", [(1, 8, 1, 1), (5, 40, 65, 3), (64, 128, 8, 2), (9, 104, 200, 8)])
+def test_router(T, H, E, k):
+    print("CASE fp32 router", T, H, E, k, flush=True)
+    g = torch.Generator(device="cuda").manual_seed(T)
+    x = torch.randint(-32, 33, (T, H), generator=g, device="cuda").float() / 32  # every sum exact
+    w = torch.randint(-32, 33, (E, H), generator=g, device="cuda").float() / 32
+    b = torch.randint(-32, 33, (E,), generator=g, device="cuda").float() / 32
+    ids, _, lg = moe.moe_gate_topk(x, w, b, k, logits=True)
+    torch.cuda.synchronize()
+    z = x.double() @ w.double().t() + b.double()
+    assert torch.equal(lg.double(), z)
+    assert torch.equal(ids.long(), torch.sort(z, dim=1, descending=True, stable=True)[1][:, :k])
