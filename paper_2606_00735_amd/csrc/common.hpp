@@ -62,17 +62,15 @@ __device__ __forceinline__ int swz_chunk(int row, int chunk) {
   return BK == 64 ? (chunk ^ ((row >> 1) & 7)) : (chunk ^ ((row >> 2) & 3));
 }
 
-// A value that is the same in every lane, moved to an SGPR. Inline asm: the
-// compiler drops the builtin where it knows the value to be uniform, and then
-// keeps what is computed from it (an integer quotient comes from the vector
-// unit) in VGPRs, chunk addresses and loop bounds among them. The compiler
-// does not look into the asm for hazards, so it holds the wait states of both
-// sides: a vector instruction that wrote v just before, and a vector memory
-// instruction that uses the SGPR next.
+// A value that is the same in every lane, moved to an SGPR. Through an empty
+// asm block: the compiler drops the builtin where it knows the value to be
+// uniform, and then keeps what is computed from it (an integer quotient comes
+// from the vector unit) in VGPRs, chunk addresses and loop bounds among them.
+// The move itself is the builtin, so the compiler keeps the wait states around
+// it, and none where nothing needs them.
 __device__ __forceinline__ int uniform_int(int v) {
-  int r;
-  asm volatile("s_nop 1\n\tv_readfirstlane_b32 %0, %1\n\ts_nop 4" : "=s"(r) : "v"(v));
-  return r;
+  asm("" : "+v"(v));
+  return __builtin_amdgcn_readfirstlane(v);
 }
 
 // LDS byte address of a pointer into LDS: the low half of a generic address

@@ -189,6 +189,7 @@ __device__ __forceinline__ void split_epilogue(const f32x16_t (&acc)[NB][MI][NI]
         float* out = pbase + b * pstride + (size_t)r0 * ld + col0 + wn * WN;
 #pragma unroll
         for (int it = 0; it < 32 * PP / 64; ++it) {
+          if (m0 + r0 + it * (64 / PP) >= m_end) break;  // a decode tile has a row or a few
           const int row = (it * 64 + lane) / PP, p = lane % PP;
           const f32x4_t v = *reinterpret_cast<const f32x4_t*>(blk + row * RB + ((p ^ key(row)) * 16));
           if (m0 + r0 + row < m_end) {
@@ -1000,27 +1001,42 @@ __device__ __forceinline__ int wave_incl_scan(int x) {
   return x;
 }
 
-template <int NV, int W>
-__device__ __forceinline__ void block_scan(int (&v)[NV], int (&excl)[NV], int (&total)[NV], int (*s_tot)[W]) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  int inc[NV];
-#pragma unroll
-  for (int q = 0; q < NV; ++q) {
-    inc[q] = wave_incl_scan(v[q]);
-    if (lane == 63) s_tot[q][wave] = inc[q];
-  }
+// What every block derives from the offsets: for this thread's expert, the
+// tiles and rows of the experts before it; over all experts, the sums.
+struct ExpertScan {
+  int tiles0, rows0;                   // of the experts before this thread's
+  int tiles, rows;                     // of all experts
+  int n_big, n_active, n_over, n_pref;  // experts above 64 rows, with rows, above the slot rows, above kSkPrefRows
+};
+// Every launch runs this before its first load, so it is kept short: the
+// instruction cache is cold then, and each line of code on the way is fetched
+// from beyond the L2 that the weights stream through. Only tiles and rows are
+// scanned; the counts are ballots, two to a word, and only the waves that hold
+// experts write theirs. Cycles from a block's first instruction to here, six
+// scans over all waves / now: gate/up 3680 / 1880, down 4100 / 2680; with the
+// wait states of uniform_int left to the compiler and 64-bit divisions out of
+// the way, FFN of one expert of 1, 16, 128 rows, us: DSV3-shaped 34.0 / 33.0,
+// 36.4 / 35.5, 69.2 / 68.1; Qwen3-shaped 19.7 / 18.6, 21.1 / 19.9, 50.6 / 49.7.
+constexpr int kScanWaves = kMaxExperts / kWave;
+__device__ __forceinline__ ExpertScan scan_experts(int tiles, int rows, int sk_rows, int pref_rows,
+                                                   int4 (&s_tot)[kScanWaves]) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int it = wave_incl_scan(tiles), ir = wave_incl_scan(rows);
+  auto count = [](bool p) { return (int)__popcll(__ballot(p)); };
+  const int c0 = count(rows > kSmallM) | count(rows > 0) << 16;
+  const int c1 = count(rows > sk_rows) | count(rows > pref_rows) << 16;
+  if (lane == 63 && wave < kScanWaves) s_tot[wave] = make_int4(it, ir, c0, c1);
   __syncthreads();
+  int bt = 0, br = 0, tt = 0, tr = 0, t0 = 0, t1 = 0;
 #pragma unroll
-  for (int q = 0; q < NV; ++q) {
-    int base = 0, tot = 0;
-#pragma unroll
-    for (int w = 0; w < W; ++w) {
-      if (w < wave) base += s_tot[q][w];
-      tot += s_tot[q][w];
-    }
-    excl[q] = base + inc[q] - v[q];
-    total[q] = uniform_int(tot);
+  for (int w = 0; w < kScanWaves; ++w) {
+    const int4 v = s_tot[w];
+    if (w < wave) bt += v.x, br += v.y;
+    tt += v.x, tr += v.y, t0 += v.z, t1 += v.w;
   }
+  t0 = uniform_int(t0), t1 = uniform_int(t1);
+  return {bt + it - tiles, br + ir - rows, uniform_int(tt), uniform_int(tr),
+          t0 & 0xffff,     t0 >> 16,       t1 & 0xffff,     t1 >> 16};
 }
 
 template <bool DUAL, int W>
@@ -1195,9 +1211,11 @@ constexpr int kSkMinChunks = 2;  // K chunks per block share, at least (when the
 // Mixtral-shaped experts: faster up to 13-16 rows, 3-10 % slower at 29-32).
 constexpr int kSkPrefRows = 16;
 // floor(n / d) for 0 <= n, 0 < d: 32-bit division when n fits (the GPU has
-// no integer divider; a 64-bit division costs several times a 32-bit one)
+// no integer divider; a 64-bit division costs several times a 32-bit one,
+// and its code is laid out of the way: see scan_experts)
 __device__ __forceinline__ long long sk_div(long long n, long long d) {
-  if (((unsigned long long)n | (unsigned long long)d) < (1ULL << 32)) return (long long)((uint32_t)n / (uint32_t)d);
+  if (__builtin_expect(((unsigned long long)n | (unsigned long long)d) < (1ULL << 32), 1))
+    return (long long)((uint32_t)n / (uint32_t)d);
   return n / d;
 }
 // Units [u0, u0 + U) shared by blocks [b0, b0 + Ga) (share order).
@@ -1373,7 +1391,8 @@ __device__ __forceinline__ void grouped_gemm_body(const GemmArgs& a) {
   __shared__ int s_row0[kMaxExperts];
   __shared__ int s_rows[kMaxExperts];
   __shared__ int s_srow0[kMaxExperts];
-  __shared__ int s_tot[6][W];
+  __shared__ int4 s_tot[kScanWaves];
+  static_assert(W >= kScanWaves, "a thread per expert");
 
   const int tid = threadIdx.x;
   const int E = a.E_local, G = gridDim.x;
@@ -1394,13 +1413,9 @@ __device__ __forceinline__ void grouped_gemm_body(const GemmArgs& a) {
     s_row0[tid] = o0;
     s_rows[tid] = rows;
   }
-  // tiles at 128 columns, rows, experts above 64 rows, experts with rows,
-  // experts above the decode schedule's slot rows and above kSkPrefRows
-  int v[6] = {row_tiles(rows) * (a.N / 128), rows, rows > kSmallM ? 1 : 0, rows > 0 ? 1 : 0,
-              rows > a.sk_rows ? 1 : 0, rows > kSkPrefRows ? 1 : 0};
-  int ex[6], tot[6];
-  block_scan<6, W>(v, ex, tot, s_tot);
-  const int T0 = tot[0], R = tot[1], n_big = tot[2], n_active = tot[3];
+  // tiles are counted at 128 columns
+  const ExpertScan sc = scan_experts(row_tiles(rows) * (a.N / 128), rows, a.sk_rows, kSkPrefRows, s_tot);
+  const int T0 = sc.tiles, R = sc.rows, n_big = sc.n_big, n_active = sc.n_active;
   // Decode schedule when every expert fits a slot's rows. Otherwise tiles
   // split along K need the reduction launch; when the host launches none
   // (it saw that no expert can exceed the slot rows, so only offsets that
@@ -1413,8 +1428,8 @@ __device__ __forceinline__ void grouped_gemm_body(const GemmArgs& a) {
   // only fill by splitting every tile) or, with no reduction launch to
   // follow, no expert exceeds 64 rows. Otherwise a launch with no reduction
   // to follow runs whole tiles in rounds.
-  const bool sk_fits = a.sk && tot[4] == 0;
-  if (sk_fits && (tot[5] == 0 || 2 * T0 <= G || (a.no_reduce && n_big == 0))) {
+  const bool sk_fits = a.sk && sc.n_over == 0;
+  if (sk_fits && (sc.n_pref == 0 || 2 * T0 <= G || (a.no_reduce && n_big == 0))) {
     // a single GEMM with at least as many 256-column tiles as blocks takes
     // them (the tile counts at 128 columns are even then): each block then
     // runs whole tiles, half as many pipeline fills (same-process A/B,
@@ -1422,7 +1437,7 @@ __device__ __forceinline__ void grouped_gemm_body(const GemmArgs& a) {
     // With fewer tiles, wider ones only split more (one expert: up to 70 %
     // slower)
     const bool dwide = !DUAL && (a.N % 256) == 0 && T0 / 2 >= G;
-    if (tid < E) s_start[tid] = dwide ? ex[0] / 2 : ex[0];
+    if (tid < E) s_start[tid] = dwide ? sc.tiles0 / 2 : sc.tiles0;
     if (tid == 0) s_xcd = xcd;
     if (blockIdx.x == 0 && tid == 0 && a.plan != nullptr) {
       a.plan[0] = 1;  // nothing for a reduction launch to do
@@ -1484,8 +1499,8 @@ __device__ __forceinline__ void grouped_gemm_body(const GemmArgs& a) {
   const int full = total - rem;
   const int n_items = full + rem * St;
   if (tid < E) {
-    s_start[tid] = ex[0] * mul / div;
-    s_srow0[tid] = ex[1];
+    s_start[tid] = sc.tiles0 * mul / div;
+    s_srow0[tid] = sc.rows0;
   }
   __syncthreads();
   if (blockIdx.x == 0 && a.plan != nullptr) {
