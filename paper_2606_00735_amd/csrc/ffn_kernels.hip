@@ -1919,8 +1919,6 @@ static long long part_cap_floats(int M_cap, int E_local, int H, int I) {
   return std::min(std::max(split_k, tail), kPartCapFloats);
 }
 
-static int device_cu_count();
-
 // the decode schedule's slots: two per block, 2 x kSkRows x 128 floats each
 static long long sk_slot_floats() { return 2LL * std::min(device_cu_count(), kMaxBlocks) * 2 * kSkRows * 128; }
 
@@ -1958,7 +1956,7 @@ size_t ffn_ws_bytes(int M_cap, int E_local, int H, int I, bool bf16) {
   return ffn_ws_layout(M_cap, E_local, H, I, bf16).bytes;
 }
 
-static int device_cu_count() {
+int device_cu_count() {
   static int cached[64] = {0};
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;

@@ -59,6 +59,9 @@ hipError_t launch_ffn_mx(const uint8_t* xq, const uint32_t* xs, const uint8_t* w
                          const int32_t* offsets, int E_local, int H, int I, int ld_gu, int ld_dn, int M_cap,
                          void* y_perm, void* ws, hipStream_t s);
 
+// compute units of the current device (256 if it cannot be asked)
+int device_cu_count();
+
 hipError_t launch_place_greedy(const double* W, int L, int E, const double* kn, const double* kt, int G, int nk,
                                int cap, int32_t* assign, double* loads, double* targets, hipStream_t s);
 hipError_t launch_place_incremental(const double* W, int L, int E, const double* kn, const double* kt, int G,

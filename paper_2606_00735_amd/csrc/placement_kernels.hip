@@ -15,9 +15,14 @@
 namespace moe {
 
 constexpr int kPlaceThreads = 256;
-constexpr int kPlaceMaxE = 1024;  // experts per layer
 constexpr int kPlaceMaxG = 64;    // GPUs (one wave holds them)
-constexpr int kPlaceMaxNk = 64;   // knots of a latency model
+
+// the bitonic sort's length: the power of two that holds E entries
+__host__ __device__ inline int place_pow2(int E) {
+  int P = 1;
+  while (P < E) P <<= 1;
+  return P;
+}
 
 // f(n) of one GPU's model: knots (kn[k], kt[k]), k < nk, kn strictly
 // increasing and positive. f = 0 for n <= 0, kt[0] up to kn[0], linear
@@ -38,16 +43,34 @@ __device__ double latency_at(const double* kn, const double* kt, int nk, double 
   return hi_t + (hi_t - lo_t) * ((n - hi_n) / (hi_n - lo_n));
 }
 
-// All G models in LDS (at most 64 x 64 knots): every block evaluates them many
-// times, each time a chain of dependent reads.
-struct Models {
-  double n[kPlaceMaxG * kPlaceMaxNk], t[kPlaceMaxG * kPlaceMaxNk];
-};
-__device__ __forceinline__ void load_models(Models& m, const double* knots_n, const double* knots_t, int G, int nk) {
-  for (int i = threadIdx.x; i < G * nk; i += blockDim.x) {
-    m.n[i] = knots_n[i];
-    m.t[i] = knots_t[i];
+// The G models, in LDS if STAGED: every block evaluates them many times, each
+// time a chain of dependent reads. All of a block's LDS that depends on the
+// sizes is one dynamic array (8-byte aligned), cut in order by Lds, so that a
+// launch of many layers keeps several blocks on a CU (see staged).
+extern __shared__ double s_dyn[];
+struct Lds {
+  char* p;
+  __device__ __forceinline__ Lds() : p(reinterpret_cast<char*>(s_dyn)) {}
+  template <class T>
+  __device__ __forceinline__ T* take(int n) {
+    T* r = reinterpret_cast<T*>(p);
+    p += (size_t)n * sizeof(T);
+    return r;
   }
+};
+struct Models {
+  const double *n, *t;
+};
+template <bool STAGED>
+__device__ __forceinline__ Models load_models(Lds& lds, const double* knots_n, const double* knots_t, int G, int nk) {
+  if constexpr (!STAGED) return {knots_n, knots_t};
+  double* n = lds.take<double>(G * nk);
+  double* t = lds.take<double>(G * nk);
+  for (int i = threadIdx.x; i < G * nk; i += blockDim.x) {
+    n[i] = knots_n[i];
+    t[i] = knots_t[i];
+  }
+  return {n, t};
 }
 
 // Sum of w[e] over the experts with a[e] == g, in ascending e (both in LDS; all
@@ -141,28 +164,26 @@ __device__ __forceinline__ double greedy_assign(const double* key, const int* id
 // ---------------------------------------------------------------------------
 // Algorithm 1, Phase 2: speed-proportional targets and descending-load greedy.
 // ---------------------------------------------------------------------------
+template <bool STAGED>
 __global__ __launch_bounds__(kPlaceThreads) void place_greedy_kernel(const double* __restrict__ W, int E,
                                                                      const double* __restrict__ knots_n,
                                                                      const double* __restrict__ knots_t, int G,
                                                                      int nk, int cap, int32_t* __restrict__ assign,
                                                                      double* __restrict__ loads,
                                                                      double* __restrict__ targets) {
-  __shared__ Models s_m;
-  __shared__ double s_w[kPlaceMaxE];
-  __shared__ double s_key[kPlaceMaxE];  // sort keys: load, descending
-  __shared__ int s_id[kPlaceMaxE];      // expert ids, ascending among equal loads
-  __shared__ int s_assign[kPlaceMaxE];
   __shared__ double s_speed[kPlaceMaxG];
   __shared__ double s_N, s_S;
   const int l = blockIdx.x, tid = threadIdx.x;
   const double* w = W + (size_t)l * E;
-  load_models(s_m, knots_n, knots_t, G, nk);
+  const int P = place_pow2(E);
+  Lds lds;
+  const Models m = load_models<STAGED>(lds, knots_n, knots_t, G, nk);
+  double* s_key = lds.take<double>(P);  // sort keys: load, descending
+  int* s_id = lds.take<int>(P);         // expert ids, ascending among equal loads
+  int* s_assign = lds.take<int>(E);
 
-  int P = 1;
-  while (P < E) P <<= 1;
   for (int i = tid; i < P; i += kPlaceThreads) {
     if (i < E) {
-      s_w[i] = w[i];
       s_key[i] = w[i];
       s_id[i] = i;
       s_assign[i] = 0;
@@ -172,16 +193,16 @@ __global__ __launch_bounds__(kPlaceThreads) void place_greedy_kernel(const doubl
     }
   }
   __syncthreads();
-  if (tid == 0) {  // N = sum_e w_e in ascending e
+  if (tid == 0) {  // N = sum_e w_e in ascending e (the keys are not sorted yet)
     double N = 0.0;
 #pragma unroll 16
-    for (int e = 0; e < E; ++e) N += s_w[e];
+    for (int e = 0; e < E; ++e) N += s_key[e];
     s_N = N;
   }
   __syncthreads();
   const double N = s_N;
   if (tid < G) {
-    s_speed[tid] = N > 0.0 ? 1.0 / latency_at(s_m.n + tid * nk, s_m.t + tid * nk, nk, N / E) : 1.0;
+    s_speed[tid] = N > 0.0 ? 1.0 / latency_at(m.n + tid * nk, m.t + tid * nk, nk, N / E) : 1.0;
   }
   __syncthreads();
   if (tid == 0) {
@@ -232,13 +253,10 @@ __global__ __launch_bounds__(kPlaceThreads) void place_greedy_kernel(const doubl
 // ---------------------------------------------------------------------------
 // Algorithm 2: swaps between the slowest and the fastest GPU.
 // ---------------------------------------------------------------------------
+template <bool STAGED>
 __global__ __launch_bounds__(kPlaceThreads) void place_incremental_kernel(
     const double* __restrict__ W, int E, const double* __restrict__ knots_n, const double* __restrict__ knots_t,
     int G, int nk, double eps, int max_swaps, int32_t* __restrict__ assign, int32_t* __restrict__ n_swaps) {
-  __shared__ Models s_m;
-  __shared__ double s_w[kPlaceMaxE];
-  __shared__ int s_a[kPlaceMaxE];
-  __shared__ int s_hi_list[kPlaceMaxE], s_lo_list[kPlaceMaxE];
   __shared__ double s_n[kPlaceMaxG], s_lat[kPlaceMaxG];
   __shared__ int s_hi, s_lo, s_nhi, s_nlo, s_stop;
   __shared__ double s_red_v[kPlaceThreads / kWave];
@@ -246,7 +264,12 @@ __global__ __launch_bounds__(kPlaceThreads) void place_incremental_kernel(
   const int l = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const double* w = W + (size_t)l * E;
   int32_t* a = assign + (size_t)l * E;
-  load_models(s_m, knots_n, knots_t, G, nk);
+  Lds lds;
+  const Models m = load_models<STAGED>(lds, knots_n, knots_t, G, nk);
+  double* s_w = lds.take<double>(E);
+  int* s_a = lds.take<int>(E);
+  int* s_hi_list = lds.take<int>(E);
+  int* s_lo_list = lds.take<int>(E);
   for (int e = tid; e < E; e += kPlaceThreads) {
     s_w[e] = w[e];
     const int g = a[e];
@@ -256,7 +279,7 @@ __global__ __launch_bounds__(kPlaceThreads) void place_incremental_kernel(
   if (tid < G) s_n[tid] = owned_sum(s_w, s_a, E, tid);  // n_g in ascending expert id
   __syncthreads();
   auto lat_of = [&](int g, double n) {
-    return latency_at(s_m.n + g * nk, s_m.t + g * nk, nk, n);
+    return latency_at(m.n + g * nk, m.t + g * nk, nk, n);
   };
   int swaps = 0;
   for (;;) {
@@ -362,6 +385,7 @@ __global__ __launch_bounds__(kPlaceThreads) void place_incremental_kernel(
 // n_g = sum_{e in S_g} w_e (ascending e), f_g(n_g), and the grouped reading
 // sum_{e in S_g} f_g(w_e). The layer latency is the maximum over GPUs.
 // ---------------------------------------------------------------------------
+template <bool STAGED>
 __global__ __launch_bounds__(kPlaceThreads) void placement_cost_kernel(const double* __restrict__ W,
                                                                        const int32_t* __restrict__ assign, int E,
                                                                        const double* __restrict__ knots_n,
@@ -369,11 +393,12 @@ __global__ __launch_bounds__(kPlaceThreads) void placement_cost_kernel(const dou
                                                                        int nk, double* __restrict__ loads,
                                                                        double* __restrict__ lat,
                                                                        double* __restrict__ lat_grouped) {
-  __shared__ Models s_m;
-  __shared__ double s_w[kPlaceMaxE], s_f[kPlaceMaxE];
-  __shared__ int s_a[kPlaceMaxE];
   const int l = blockIdx.x, tid = threadIdx.x;
-  load_models(s_m, knots_n, knots_t, G, nk);
+  Lds lds;
+  const Models m = load_models<STAGED>(lds, knots_n, knots_t, G, nk);
+  double* s_w = lds.take<double>(E);
+  double* s_f = lds.take<double>(E);
+  int* s_a = lds.take<int>(E);
   for (int e = tid; e < E; e += kPlaceThreads) {
     s_w[e] = W[(size_t)l * E + e];
     s_a[e] = assign[(size_t)l * E + e];
@@ -382,7 +407,7 @@ __global__ __launch_bounds__(kPlaceThreads) void placement_cost_kernel(const dou
   // every expert's own latency side by side, then two sums per GPU
   for (int e = tid; e < E; e += kPlaceThreads) {
     const int g = s_a[e];
-    if (g >= 0 && g < G) s_f[e] = latency_at(s_m.n + g * nk, s_m.t + g * nk, nk, s_w[e]);
+    if (g >= 0 && g < G) s_f[e] = latency_at(m.n + g * nk, m.t + g * nk, nk, s_w[e]);
   }
   __syncthreads();
   const int g = tid & (kPlaceMaxG - 1), which = tid / kPlaceMaxG;  // one wave per sum
@@ -390,7 +415,7 @@ __global__ __launch_bounds__(kPlaceThreads) void placement_cost_kernel(const dou
   if (which == 0) {
     const double n = owned_sum(s_w, s_a, E, g);
     if (loads) loads[(size_t)l * G + g] = n;
-    lat[(size_t)l * G + g] = latency_at(s_m.n + g * nk, s_m.t + g * nk, nk, n);
+    lat[(size_t)l * G + g] = latency_at(m.n + g * nk, m.t + g * nk, nk, n);
   } else if (which == 1 && lat_grouped) {
     lat_grouped[(size_t)l * G + g] = owned_sum(s_f, s_a, E, g);
   }
@@ -470,10 +495,25 @@ __global__ __launch_bounds__(kDriftThreads) void drift_distance_kernel(const dou
 // ---------------------------------------------------------------------------
 // Launchers
 // ---------------------------------------------------------------------------
+// Models go to LDS where they are small (16 KB: three blocks a CU or more with
+// the largest layers) or where a CU gets one block anyway; else blocks read
+// them from the caches. Room for the largest models in every block left one
+// block a CU; us, so / by sizes: 1000 layers of 64 experts, 8 GPUs of 4 knots,
+// greedy 84 / 24, incremental 63 / 31; 600 layers of 1024 experts, 64 GPUs of
+// 64 knots (not staged), greedy 1524 / 550, incremental 407 / 162, cost 90 / 42;
+// 58 layers of 256, 8 of 14: greedy 72.9 / 73.6, incremental 74.6 / 74.3. Below
+// one block a CU staging is what pays: 64 layers of 1024, 64 of 64, incremental
+// 277 from the caches, 138 from LDS.
+static bool staged(int L, int G, int nk) { return G * nk <= 1024 || L <= device_cu_count(); }
+static size_t model_bytes(bool st, int G, int nk) { return st ? (size_t)2 * G * nk * sizeof(double) : 0; }
+
 hipError_t launch_place_greedy(const double* W, int L, int E, const double* kn, const double* kt, int G, int nk,
                                int cap, int32_t* assign, double* loads, double* targets, hipStream_t s) {
   if (L == 0) return hipSuccess;
-  place_greedy_kernel<<<L, kPlaceThreads, 0, s>>>(W, E, kn, kt, G, nk, cap, assign, loads, targets);
+  const bool st = staged(L, G, nk);
+  const size_t lds = model_bytes(st, G, nk) + (size_t)place_pow2(E) * 12 + (size_t)E * 4;
+  const auto kernel = st ? place_greedy_kernel<true> : place_greedy_kernel<false>;
+  kernel<<<L, kPlaceThreads, lds, s>>>(W, E, kn, kt, G, nk, cap, assign, loads, targets);
   return hipGetLastError();
 }
 
@@ -481,7 +521,10 @@ hipError_t launch_place_incremental(const double* W, int L, int E, const double*
                                     int nk, double eps, int max_swaps, int32_t* assign, int32_t* n_swaps,
                                     hipStream_t s) {
   if (L == 0) return hipSuccess;
-  place_incremental_kernel<<<L, kPlaceThreads, 0, s>>>(W, E, kn, kt, G, nk, eps, max_swaps, assign, n_swaps);
+  const bool st = staged(L, G, nk);
+  const auto kernel = st ? place_incremental_kernel<true> : place_incremental_kernel<false>;
+  kernel<<<L, kPlaceThreads, model_bytes(st, G, nk) + (size_t)E * 20, s>>>(W, E, kn, kt, G, nk, eps, max_swaps,
+                                                                           assign, n_swaps);
   return hipGetLastError();
 }
 
@@ -489,7 +532,10 @@ hipError_t launch_placement_cost(const double* W, const int32_t* assign, int L, 
                                  const double* kt, int G, int nk, double* loads, double* lat, double* lat_grouped,
                                  hipStream_t s) {
   if (L == 0) return hipSuccess;
-  placement_cost_kernel<<<L, kPlaceThreads, 0, s>>>(W, assign, E, kn, kt, G, nk, loads, lat, lat_grouped);
+  const bool st = staged(L, G, nk);
+  const auto kernel = st ? placement_cost_kernel<true> : placement_cost_kernel<false>;
+  kernel<<<L, kPlaceThreads, model_bytes(st, G, nk) + (size_t)E * 20, s>>>(W, assign, E, kn, kt, G, nk, loads, lat,
+                                                                           lat_grouped);
   return hipGetLastError();
 }
 
