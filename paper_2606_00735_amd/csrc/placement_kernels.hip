@@ -433,6 +433,11 @@ __global__ void window_push_kernel(const int32_t* __restrict__ counts, int32_t* 
   ring_slot[i] = c;
 }
 
+__device__ __forceinline__ double cosine_distance(double dot, double na, double nb) {
+  if (na == 0.0 || nb == 0.0) return (na == nb) ? 0.0 : 1.0;
+  return 1.0 - dot / (__builtin_sqrt(na) * __builtin_sqrt(nb));
+}
+
 // One block, so that the trigger (the OR of d > delta over all layers, written
 // by thread 0) needs no atomics and no memset. Each of its 16 waves takes
 // kDriftLayers layers at a time: the lanes read 64 experts of each, coalesced,
@@ -479,14 +484,34 @@ __global__ __launch_bounds__(kDriftThreads) void drift_distance_kernel(const dou
     const double dot = shfl_f64(sum, (3 * lane) & 63), na = shfl_f64(sum, (3 * lane + 1) & 63),
                  nb = shfl_f64(sum, (3 * lane + 2) & 63);
     if (lane < kDriftLayers && lw + lane < L) {
-      double dist;
-      if (na == 0.0 || nb == 0.0)
-        dist = (na == nb) ? 0.0 : 1.0;
-      else
-        dist = 1.0 - dot / (__builtin_sqrt(na) * __builtin_sqrt(nb));
+      const double dist = cosine_distance(dot, na, nb);
       d[lw + lane] = dist;
       over = over || dist > delta;
     }
+  }
+  const int any = __syncthreads_or(over ? 1 : 0);
+  if (threadIdx.x == 0 && trigger) *trigger = any ? 1 : 0;
+}
+
+// The same sums with a thread per layer, for layers of so few experts that the
+// waves above would be mostly empty (see launch_drift_distance).
+__global__ __launch_bounds__(256) void drift_distance_few_kernel(const double* __restrict__ w_cur,
+                                                                 const double* __restrict__ w_ref, int L, int E,
+                                                                 double delta, double* __restrict__ d,
+                                                                 int32_t* __restrict__ trigger) {
+  bool over = false;
+  for (int l = threadIdx.x; l < L; l += 256) {
+    const double* u = w_cur + (size_t)l * E;
+    const double* v = w_ref + (size_t)l * E;
+    double dot = 0.0, na = 0.0, nb = 0.0;
+    for (int e = 0; e < E; ++e) {
+      dot += u[e] * v[e];
+      na += u[e] * u[e];
+      nb += v[e] * v[e];
+    }
+    const double dist = cosine_distance(dot, na, nb);
+    d[l] = dist;
+    over = over || dist > delta;
   }
   const int any = __syncthreads_or(over ? 1 : 0);
   if (threadIdx.x == 0 && trigger) *trigger = any ? 1 : 0;
@@ -549,7 +574,15 @@ hipError_t launch_window_push(const int32_t* counts, int32_t* ring, double* sums
 
 hipError_t launch_drift_distance(const double* w_cur, const double* w_ref, int L, int E, double delta, double* d,
                                  int32_t* trigger, hipStream_t s) {
-  drift_distance_kernel<<<1, kDriftThreads, 0, s>>>(w_cur, w_ref, L, E, delta, d, trigger);
+  // A round of drift_distance_kernel (64 layers x 64 experts, or what there is)
+  // takes about 13 times an expert of drift_distance_few_kernel's 256 layers:
+  // 4000 layers of 16 experts 149 / 60 us, 1000 of 64 56 / 57, 300 of 128
+  // 32 / 43, 58 of 256 13.6 / 32.
+  const long long rounds = (long long)((L + 63) / 64) * ((E + kWave - 1) / kWave);
+  if (13 * rounds > (long long)((L + 255) / 256) * E && E < kWave)
+    drift_distance_few_kernel<<<1, 256, 0, s>>>(w_cur, w_ref, L, E, delta, d, trigger);
+  else
+    drift_distance_kernel<<<1, kDriftThreads, 0, s>>>(w_cur, w_ref, L, E, delta, d, trigger);
   return hipGetLastError();
 }
 

@@ -81,3 +81,29 @@ def test_blocks_share_a_cu():
     print("greedy, incremental us: 64 layers", few, "1024 layers", many, flush=True)
     assert many[0] <= 2.0 * few[0]
     assert many[1] <= 2.0 * few[1]
+
+
+@pytest.mark.parametrize("L,E", [(1, 12), (257, 3), (600, 63), (4096, 16), (65, 64), (300, 130)])
+def test_drift_matches_oracle(L, E):
+    print("CASE drift", L, E, flush=True)
+    W, _, _, _ = _problem(L, E, 2, 1, L)
+    V, _, _, _ = _problem(L, E, 2, 1, L + 1)
+    W[0] = 0.0
+    d, trig = moe.moe_drift_distance(_dev(W), _dev(V), delta=0.05)
+    d = d.cpu().numpy()
+    for l in range(L):
+        assert d[l] == P.cosine_distance(W[l], V[l]), f"layer {l}"
+    assert int(trig.item()) == int(d.max() > 0.05)
+
+
+def test_drift_of_few_experts():
+    """The same loads as 4096 layers of 16 experts and as 1024 of 64: about the
+    same time (with waves three quarters empty the first takes 2.7 times as long)."""
+    W, _, _, _ = _problem(1024, 64, 2, 1, 3)
+    us = []
+    for L, E in ((1024, 64), (4096, 16)):
+        w, d = _dev(W).view(L, E), torch.empty(L, dtype=torch.float64, device="cuda")
+        t = torch.empty(1, dtype=torch.int32, device="cuda")
+        us.append(best_us(lambda: moe.moe_drift_distance(w, w, d=d, trigger=t)))
+    print("drift us", us, flush=True)
+    assert us[1] <= 1.7 * us[0]
