@@ -1776,17 +1776,21 @@ __global__ __launch_bounds__(256) void split_reduce_mx_kernel(const float* __res
 // ---------------------------------------------------------------------------
 constexpr int kF32Lanes = 8;             // lanes per column
 constexpr int kF32Cols = 256 / kF32Lanes;  // columns per block
+constexpr int kF32Blocks = 8192, kF32Rows = 1024;  // blocks of a launch and rows at a time, at least (see launch_ffn)
 
-// The expert whose range holds `row` (the same in every lane), or -1.
+// The expert whose range holds `row` (the same in every lane), -1 if there is
+// none, -2 if none holds any row from `row` on.
 __device__ __forceinline__ int find_slot(const int32_t* offsets, int E, int M_cap, int row) {
+  uint64_t later = 0;
   for (int e0 = 0; e0 < E; e0 += kWave) {
     const int e = min(e0 + (int)(threadIdx.x & 63), E - 1);
     const int o0 = min(max(offsets[e], 0), M_cap);
     const int o1 = min(max(offsets[e + 1], o0), M_cap);
     const uint64_t in = __ballot(row >= o0 && row < o1);
     if (in != 0) return e0 + __ffsll((unsigned long long)in) - 1;
+    later |= __ballot(row < o0 && o0 < o1);
   }
-  return -1;
+  return later != 0 ? -1 : -2;
 }
 
 // Sum over the 8 lanes of a column, in each of them: lanes l ^ 1, l ^ 2, then
@@ -1816,6 +1820,7 @@ __global__ __launch_bounds__(256) void gateup_f32_kernel(const float* __restrict
   const int q = threadIdx.x % kF32Lanes;
   for (int row = blockIdx.x; row < M_cap; row += gridDim.x) {
     const int e = find_slot(offsets, E, M_cap, row);
+    if (e == -2) return;
     if (e < 0) continue;
     const float4* x = reinterpret_cast<const float4*>(X + (size_t)row * H);
     for (int i0 = blockIdx.y * kF32Cols; i0 < I; i0 += gridDim.y * kF32Cols) {
@@ -1843,6 +1848,7 @@ __global__ __launch_bounds__(256) void down_f32_kernel(const float* __restrict__
   const int q = threadIdx.x % kF32Lanes;
   for (int row = blockIdx.x; row < M_cap; row += gridDim.x) {
     const int e = find_slot(offsets, E, M_cap, row);
+    if (e == -2) return;
     if (e < 0) continue;
     const float4* hr = reinterpret_cast<const float4*>(h + (size_t)row * I);
     for (int c0 = blockIdx.y * kF32Cols; c0 < H; c0 += gridDim.y * kF32Cols) {
@@ -2084,10 +2090,15 @@ hipError_t launch_ffn(const void* x_perm, const void* w_gate, const void* w_up, 
   char* wsb = static_cast<char*>(ws);
   void* h = wsb + L.h;
   if (!bf16) {
-    // within the limits of a launch (2^32 threads in x, 65535 blocks in y);
-    // the kernels loop over what is beyond
+    // Enough blocks for every CU several times over, and the rows of an expert
+    // side by side (they share its weights in the L2: with 93 rows at a time
+    // 1000 rows over 16 experts, H = 1024, I = 2816, took 2787 us, with all of
+    // them 2006); the kernels loop over the rest. M_cap counts rows of remote
+    // experts too: with a block per row of it, 128 local rows of 65536 (H = 128,
+    // I = 256) took 256 us, now 12.
     auto grid = [&](int N) {
-      return dim3((unsigned)std::min(M_cap, 1 << 22), (unsigned)std::min((N - 1) / kF32Cols + 1, 65535));
+      const int cols = std::min((N - 1) / kF32Cols + 1, 65535);
+      return dim3((unsigned)std::min(M_cap, std::max(kF32Blocks / cols, kF32Rows)), (unsigned)cols);
     };
     gateup_f32_kernel<<<grid(I), 256, 0, s>>>(
         static_cast<const float*>(x_perm), static_cast<const float*>(w_gate), static_cast<const float*>(w_up),
