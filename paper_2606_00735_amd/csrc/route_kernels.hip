@@ -556,7 +556,16 @@ __global__ __launch_bounds__(256) void gate_topk_f32_kernel(
 #pragma unroll
         for (int i = 0; i < 32; ++i) s = __builtin_fmaf(xv[i], wv[i], s);
       }
-      for (; h < H; ++h) s = __builtin_fmaf(xr[h], w[h], s);
+      for (; h < H; h += 8) {  // H is a multiple of 8
+        float xv[8], wv[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          xv[i] = xr[h + i];
+          wv[i] = w[h + i];
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) s = __builtin_fmaf(xv[i], wv[i], s);
+      }
       z = s + (bias != nullptr ? bias[e] : 0.0f);
       if (logits != nullptr) logits[(size_t)row * E + e] = z;
     }

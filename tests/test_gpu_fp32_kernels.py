@@ -53,7 +53,7 @@ def test_ffn(H, I, rows):
         r0 += n
 
 
-@pytest.mark.parametrize("T,H,E,k", [(1, 8, 1, 1), (5, 40, 65, 3), (64, 128, 8, 2), (9, 104, 200, 8)])
+@pytest.mark.parametrize("T,H,E,k", [(1, 8, 1, 1), (5, 40, 65, 3), (64, 128, 8, 2), (9, 104, 200, 8), (3, 24, 8, 2), (7, 56, 9, 4)])
 def test_router(T, H, E, k):
     print("CASE fp32 router", T, H, E, k, flush=True)
     g = torch.Generator(device="cuda").manual_seed(T)
