@@ -1513,11 +1513,13 @@ __device__ __forceinline__ void grouped_gemm_body(const GemmArgs& a) {
     }
     if (S > 1 && tid < E)
       for (int r = 0; r < s_rows[tid]; ++r) a.plan[kPlanHead + s_srow0[tid] + r] = s_row0[tid] + r;
-    if (St > 1 && tid < rem) {
-      const TileRef t = decode_tile<false>(full + tid, E, s_start, s_row0, s_rows, cols, a.N);
-      a.plan[kPlanHead + 3 * tid] = t.m0;
-      a.plan[kPlanHead + 3 * tid + 1] = t.m_end;
-      a.plan[kPlanHead + 3 * tid + 2] = t.n0;
+    if (St > 1) {  // rem is at most G / 2, up to 512, which may be more than the block's threads
+      for (int q = tid; q < rem; q += W * kWave) {
+        const TileRef t = decode_tile<false>(full + q, E, s_start, s_row0, s_rows, cols, a.N);
+        a.plan[kPlanHead + 3 * q] = t.m0;
+        a.plan[kPlanHead + 3 * q + 1] = t.m_end;
+        a.plan[kPlanHead + 3 * q + 2] = t.n0;
+      }
     }
   }
 
