@@ -558,7 +558,12 @@ __device__ __forceinline__ void gemm_tile_mx(const GemmArgs& a, bf16_t* smem, in
     char* sl = reinterpret_cast<char*>(st);
     const uint32_t l0 = lds_addr(st) + wave * (RPI * 128);
     constexpr int LS = W * RPI * 128;  // LDS bytes between a wave's loads
-    auto mine = [&](int) { return part <= 0; };  // a burst: parts measured 0.7 % slower at decode
+    // 4 waves: in parts, as in gemm_tile (a burst of a wave's 10 to 20 loads holds
+    // up the MFMAs of the SIMD's only wave); 8 waves: all at once, parts measured
+    // 0.7 % slower at decode. FFN us, down GEMM on 4 waves, at once / in parts,
+    // Mixtral-shaped with 4, 2 and 1 of the experts, T = 4096: 805 / 765, 337 / 326,
+    // 197 / 189; Maverick-shaped shard, T = 32768: 716 / 686.
+    auto mine = [&](int t) { return part < 0 || (W == 4 && St::NS > 2 ? t * KS / St::LOADS : 0) == part; };
 #pragma unroll
     for (int t = 0; t < LA; ++t)
       if (mine(t)) dma16a(uniform_ptr(A + (size_t)kcl * kMxChunk), offA[t], l0 + t * LS);
