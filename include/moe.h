@@ -235,6 +235,21 @@ moe_status moe_grouped_swiglu_ffn_gather(const void* x, const int32_t* perm_src,
                                          void* y_perm, void* ws, size_t* ws_bytes, hipStream_t stream);
 
 /*
+ * moe_grouped_swiglu_ffn_gather_of - moe_grouped_swiglu_ffn_gather in a layer
+ * of E experts (E_local <= E <= MOE_MAX_EXPERTS; 0: not known, the same call).
+ *
+ * Same results, bit for bit. M_cap bounds the rows of the local experts, but
+ * does not say what part of T*k they hold; with E the library expects T*k/E
+ * rows an expert and launches the kernels that suit those, where it otherwise
+ * launches two for a GEMM of many rows and lets the offsets choose.
+ */
+moe_status moe_grouped_swiglu_ffn_gather_of(const void* x, const int32_t* perm_src, int T, int k,
+                                            const void* w_gate, const void* w_up, const void* w_down,
+                                            const int32_t* offsets, int E, int E_local, int H, int I,
+                                            int ldw_gu, int ldw_dn, int M_cap, moe_dtype dt,
+                                            void* y_perm, void* ws, size_t* ws_bytes, hipStream_t stream);
+
+/*
  * moe_grouped_swiglu_ffn_noalloc - moe_grouped_swiglu_ffn for callers that
  * cannot allocate device memory (code under HIP graph capture, tight serving
  * loops, harnesses that forbid allocation).

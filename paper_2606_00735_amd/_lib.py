@@ -26,7 +26,8 @@ EXPORTED = ("moe_status_string", "moe_abi_version", "moe_gate_topk", "moe_expert
             "moe_fit_latency_model", "moe_place_greedy", "moe_place_incremental", "moe_placement_cost",
             "moe_window_push", "moe_drift_distance", "moe_mx_quantize", "moe_grouped_swiglu_mx",
             "moe_grouped_gemm_mx", "moe_grouped_swiglu_ffn_mx", "moe_load_sweep_mx",
-            "moe_grouped_swiglu_ffn_gather", "moe_grouped_swiglu_ffn_noalloc", "moe_ffn_scratch_bytes")
+            "moe_grouped_swiglu_ffn_gather", "moe_grouped_swiglu_ffn_gather_of",
+            "moe_grouped_swiglu_ffn_noalloc", "moe_ffn_scratch_bytes")
 
 
 class MoeError(RuntimeError):
@@ -66,6 +67,9 @@ def load_library(path: str = LIB_PATH):
     L.moe_grouped_swiglu_ffn_gather.restype = _I
     L.moe_grouped_swiglu_ffn_gather.argtypes = [_P, _P, _I, _I, _P, _P, _P, _P, _I, _I, _I, _I, _I, _I, _I, _P, _P,
                                                 _PSZ, _P]
+    L.moe_grouped_swiglu_ffn_gather_of.restype = _I
+    L.moe_grouped_swiglu_ffn_gather_of.argtypes = [_P, _P, _I, _I, _P, _P, _P, _P, _I, _I, _I, _I, _I, _I, _I, _I, _P,
+                                                   _P, _PSZ, _P]
     L.moe_unpermute_combine.restype = _I
     L.moe_unpermute_combine.argtypes = [_P, _P, _P, _I, _I, _I, _I, _I, _P, _P]
     L.moe_load_sweep.restype = _I
@@ -357,9 +361,11 @@ def moe_grouped_swiglu_ffn_noalloc(x_perm, w_gate, w_up, w_down, offsets, y_perm
     return y_perm
 
 
-def moe_grouped_swiglu_ffn_gather(x, perm_src, k, w_gate, w_up, w_down, offsets, ws=None, y_perm=None):
+def moe_grouped_swiglu_ffn_gather(x, perm_src, k, w_gate, w_up, w_down, offsets, ws=None, y_perm=None, experts=0):
     """The grouped SwiGLU FFN reading row r of its input as x[perm_src[r] // k]
-    (bf16). Same results as moe_permute + moe_grouped_swiglu_ffn. Returns
+    (bf16). Same results as moe_permute + moe_grouped_swiglu_ffn. ``experts``:
+    the experts of the whole layer, if known; from them and T the library knows
+    how many rows to expect (the results are the same). Returns
     (y_perm [M_cap,H], ws)."""
     L = load_library()
     T, H = x.shape
@@ -376,10 +382,11 @@ def moe_grouped_swiglu_ffn_gather(x, perm_src, k, w_gate, w_up, w_down, offsets,
     y_perm = torch.empty((M_cap, H), dtype=x.dtype, device=x.device) if y_perm is None else y_perm
     n = ctypes.c_size_t(ws.numel() * ws.element_size())
     pg, pu, pd, ld_gu, ld_dn = _ffn_weights(w_gate, w_up, w_down, x.dtype)
-    st = L.moe_grouped_swiglu_ffn_gather(_dev(x, "x"), _dev(perm_src, "perm_src", torch.int32), T, k,
-                                         pg, pu, pd, _dev(offsets, "offsets", torch.int32),
-                                         E_local, H, I, ld_gu, ld_dn, M_cap, dt, _dev(y_perm, "y_perm", x.dtype),
-                                         _dev(ws, "ws"), ctypes.byref(n), _stream())
+    st = L.moe_grouped_swiglu_ffn_gather_of(_dev(x, "x"), _dev(perm_src, "perm_src", torch.int32), T, k,
+                                            pg, pu, pd, _dev(offsets, "offsets", torch.int32),
+                                            experts, E_local, H, I, ld_gu, ld_dn, M_cap, dt,
+                                            _dev(y_perm, "y_perm", x.dtype), _dev(ws, "ws"), ctypes.byref(n),
+                                            _stream())
     _check("moe_grouped_swiglu_ffn_gather", st)
     return y_perm, ws
 
@@ -455,7 +462,7 @@ def moe_layer(x, w_router, bias, k, expert_map, w_gate, w_up, w_down, logits=Fal
                                          perm_src=b.get("perm_src"), dest=b.get("dest"), gather=not fuse_gather)
     if fuse_gather:
         y_perm, fws = moe_grouped_swiglu_ffn_gather(x, perm_src, k, w_gate, w_up, w_down, offsets,
-                                                    ws=b.get("ffn_ws"), y_perm=b.get("y_perm"))
+                                                    ws=b.get("ffn_ws"), y_perm=b.get("y_perm"), experts=E)
     else:
         y_perm, fws = moe_grouped_swiglu_ffn(x_perm, w_gate, w_up, w_down, offsets, ws=b.get("ffn_ws"),
                                              y_perm=b.get("y_perm"))

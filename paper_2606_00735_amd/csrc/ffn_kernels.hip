@@ -106,6 +106,9 @@ struct GemmArgs {
   // runs on XCD b % 8), or nullptr. The decode schedule reads it to choose
   // L2-local partial sums; results do not depend on it.
   const int32_t* xcd_state;
+  // 0: the launch's kernel runs; 1: of the 4-wave and the 8-wave kernel that are
+  // launched one after the other, the one that `four` (grouped_gemm_body) names
+  int pick = 0;
 };
 
 // Split-K plan written by block 0 of a grouped GEMM for split_reduce_kernel:
@@ -1421,6 +1424,19 @@ __device__ __forceinline__ void grouped_gemm_body(const GemmArgs& a) {
   // tiles are counted at 128 columns
   const ExpertScan sc = scan_experts(row_tiles(rows) * (a.N / 128), rows, a.sk_rows, kSkPrefRows, s_tot);
   const int T0 = sc.tiles, R = sc.rows, n_big = sc.n_big, n_active = sc.n_active;
+  // Single-output GEMM: 256-column tiles move a third fewer bytes per MFMA
+  // than 128-column ones but halve the tile count; use them when every CU
+  // still gets at least two of them.
+  const bool wide = !DUAL && (a.N % 256 == 0) && (T0 / 2 >= 2 * G);
+  if (a.pick) {
+    // Which of the two kernels runs (see waves_for): rows per
+    // row tile say how much of the work is in 256-row tiles, the tile count
+    // whether the launch fills the chip with them.
+    const int row_t = T0 / (a.N / 128);
+    const bool four = DUAL ? R >= 88 * row_t && (4 * T0 >= 3 * G || R >= 1024 * n_active)
+                           : wide && R >= 176 * row_t;
+    if (four != (W == 4)) return;
+  }
   // Decode schedule when every expert fits a slot's rows. Otherwise tiles
   // split along K need the reduction launch; when the host launches none
   // (it saw that no expert can exceed the slot rows, so only offsets that
@@ -1453,10 +1469,6 @@ __device__ __forceinline__ void grouped_gemm_body(const GemmArgs& a) {
     return;
   }
 
-  // Single-output GEMM: 256-column tiles move a third fewer bytes per MFMA
-  // than 128-column ones but halve the tile count; use them when every CU
-  // still gets at least two of them.
-  const bool wide = !DUAL && (a.N % 256 == 0) && (T0 / 2 >= 2 * G);
   constexpr int CK = MX ? kMxChunk : kBK;  // K elements per chunk
   constexpr int EB = MX ? 1 : 2;           // weight bytes per element (MX scales aside)
   const int nK = a.K / CK;
@@ -2065,33 +2077,62 @@ static const int32_t* xcd_state(hipStream_t s) {
 }
 
 // Whether a GEMM launch takes 4-wave blocks (the large tile, see big_tile) or
-// 8-wave ones, from what the host knows: M_cap bounds the rows of all local
-// experts, and under expert parallelism most of it belongs to remote ones (the
-// measured shards hold an eighth). 4 waves pay where 256-row tiles do most of
-// the work and lose on the small and mid tiles, which stream weights: same
-// box, us, 8 / 4 waves:
-//   gate/up  DSV3-shaped shard T = 600 318 / 341, 1500 331 / 335, 4000 453 /
-//            411, 16384 986 / 898; Maverick-shaped 9000 492 / 498, 18000 261 /
-//            263, 32768 903 / 815; Mixtral-shaped 4096 1723 / 1633; Qwen3-shaped
-//            8192 448 / 448; MXFP8 Mixtral-shaped 4096 916 / 870
-//   down     DSV3-shaped 16384 515 / 526, Maverick-shaped 32768 507 / 535,
-//            Qwen3-shaped 8192 271 / 303, one Mixtral-shaped expert of 4000 rows
-//            (128-column tiles) 404 / 439; Mixtral-shaped 4096 859 / 785, MXFP8
-//            481 / 406
-// So gate/up takes them from 1024 rows of M_cap per local expert on (128 real
-// rows an expert in an eight-way shard, where half of the tiles are large);
-// the down GEMM, whose tail tiles weigh more, only when in addition at most 8
-// experts share the rows (large experts even if the share is an eighth of a
-// layer) and the launch has the tiles for 256-column ones (see `wide`).
-static bool four_waves(bool dual, int M_cap, int E_local, int N) {
-  if (M_cap <= kSkHostRows || (long long)M_cap < 1024LL * E_local) return false;
-  return dual || (E_local <= 8 && (long long)M_cap * N >= 1LL << 25);
+// 8-wave ones. 4 waves pay where 256-row tiles do the work and lose on the small
+// and mid tiles, which stream weights, on launches of too few tiles, and below
+// 4096 in K, where the longer fill of their pipeline shows. The results are the
+// same bits. Same box, FFN us, gate/up on 8 / 4 waves (down on 8):
+//   rows an expert   64         128        256        512         1024
+//   Mixtral-shaped   520 / 523  623 / 619  964 / 925  1542 / 1499  2629 / 2556
+//     2 of 8 experts 158 / 160  169 / 172  248 / 242   394 /  380   577 /  564
+//     1 of 8          96 /  99  112 / 119  197 / 197   199 /  189   294 /  289
+//   DSV3, 32 of 256  522 / 526  671 / 636 1010 / 946  1590 / 1498
+//      8 of 256      205 / 210  219 / 219  299 / 268   379 /  374
+//      4 of 256      102 / 111  123 / 127  143 / 154   210 /  220
+//   Maverick, 16/128 754 / 756  891 / 859 1266 / 1198
+//   Qwen3-shaped (K = 2048)                466 / 463   728 /  723
+//   MXFP8 Mixtral    284 / 298  355 / 377  534 / 541   865 /  827  1462 / 1421
+//   MXFP8 DSV3       301 / 309  380 / 373  563 / 535   851 /  807
+// and with the down GEMM on 4 waves instead, 1024 rows an expert (256-column
+// tiles) 2629 / 2565, MXFP8 1446 / 1381; 750 rows (128-column) 1889 / 1921, MXFP8
+// 1069 / 1163; K = 2048 (DSV3) within 2 % either way.
+// rows > 0: the rows an expert is expected to have (a layer's tokens x top-k over
+// all its experts: a placement that balances the GPUs leaves about that to each).
+// Without it M_cap says only what the local experts hold at most, all of it or,
+// in a shard, a small part: from 1024 rows of it per local expert on (128 in an
+// eighth of a layer) both kernels are launched, each reads the offsets, and the
+// one that they do not suit ends at once, which costs 2-4 us (one DSV3-shaped
+// expert of 1024 rows 174 / 178; 44 rows an expert in 4 of 256, MXFP8, 76 / 66).
+enum class Waves { k8, k4, kPick };
+static Waves waves_for(bool dual, int M_cap, int E_local, int N, int K, int rows) {
+  if (M_cap <= kSkHostRows || K < 4096) return Waves::k8;
+  const double G = device_cu_count(), cols = N / 128;
+  if (rows > 0) {
+    const double tiles = E_local * (rows / 256.0 + 0.5) * cols;  // half a row tile of remainder each
+    if (dual) return rows >= 128 && (tiles >= 0.75 * G || rows >= 1024) ? Waves::k4 : Waves::k8;
+    return E_local <= 8 && tiles >= 4.0 * G ? Waves::k4 : Waves::k8;
+  }
+  if (M_cap < 1024LL * E_local) return Waves::k8;
+  // down: only with 256-column tiles (`wide`), if M_cap has room for enough of them
+  const bool may = dual || (E_local <= 8 && (M_cap / 256.0 + E_local) * cols >= 4.0 * G);
+  return may ? Waves::kPick : Waves::k8;
+}
+
+template <class Kernel>
+static hipError_t launch_waves(Waves w, GemmArgs& g, unsigned grid, hipStream_t s, Kernel* four, Kernel* eight) {
+  g.pick = w == Waves::kPick ? 1 : 0;
+  if (w != Waves::k8) {
+    four<<<grid, 4 * kWave, 0, s>>>(g);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  if (w != Waves::k4) eight<<<grid, 8 * kWave, 0, s>>>(g);
+  return hipGetLastError();
 }
 
 hipError_t launch_ffn(const void* x_perm, const void* w_gate, const void* w_up, const void* w_down,
                       const int32_t* offsets, int E_local, int H, int I, int ld_gu, int ld_dn, int M_cap, bool bf16,
                       void* y_perm, void* ws, hipStream_t s, const int32_t* a_src, int a_div, int a_T,
-                      size_t ws_cap) {
+                      size_t ws_cap, int rows) {
   if (E_local == 0 || M_cap == 0) return hipSuccess;
   const FfnWs L = ffn_ws_layout(M_cap, E_local, H, I, bf16, ws_cap);
   char* wsb = static_cast<char*>(ws);
@@ -2158,11 +2199,8 @@ hipError_t launch_ffn(const void* x_perm, const void* w_gate, const void* w_up, 
   g1.skpart = part;
   g1.tcnt = cnt + kTcntGU;
   g1.xcd_state = L.sk_ok ? xcd_state(s) : nullptr;
-  if (!sk && four_waves(true, M_cap, E_local, I))
-    grouped_gemm_bf16_kernel<true, 4><<<grid_for(I), 4 * kWave, 0, s>>>(g1);
-  else
-    grouped_gemm_bf16_kernel<true, 8><<<grid_for(I), 8 * kWave, 0, s>>>(g1);
-  hipError_t e = hipGetLastError();
+  hipError_t e = launch_waves(sk ? Waves::k8 : waves_for(true, M_cap, E_local, I, H, rows), g1, grid_for(I), s,
+                   grouped_gemm_bf16_kernel<true, 4>, grouped_gemm_bf16_kernel<true, 8>);
   if (e != hipSuccess) return e;
   // A GEMM can split only if its K range holds two splits of kMinSplitChunks.
   const bool split_gu = H / kBK >= 2 * kMinSplitChunks, split_dn = I / kBK >= 2 * kMinSplitChunks;
@@ -2182,11 +2220,8 @@ hipError_t launch_ffn(const void* x_perm, const void* w_gate, const void* w_up, 
   g2.skpart = part;
   g2.tcnt = cnt + kTcntDN;
   g2.xcd_state = g1.xcd_state;
-  if (!sk && four_waves(false, M_cap, E_local, H))
-    grouped_gemm_bf16_kernel<false, 4><<<grid_for(H), 4 * kWave, 0, s>>>(g2);
-  else
-    grouped_gemm_bf16_kernel<false, 8><<<grid_for(H), 8 * kWave, 0, s>>>(g2);
-  e = hipGetLastError();
+  e = launch_waves(sk ? Waves::k8 : waves_for(false, M_cap, E_local, H, I, rows), g2, grid_for(H), s,
+                   grouped_gemm_bf16_kernel<false, 4>, grouped_gemm_bf16_kernel<false, 8>);
   if (e != hipSuccess) return e;
   if (split_dn && !sk)
     split_reduce_kernel<false><<<reduce_grid(H), 256, 0, s>>>(part, plan, H, static_cast<bf16_t*>(y_perm));
@@ -2270,7 +2305,7 @@ static void mx_split_args(GemmArgs& g, const MxSplit& sp) {
 static hipError_t gateup_mx(const uint8_t* xq, const uint32_t* xs, const uint8_t* wgq, const uint32_t* wgs,
                             const uint8_t* wuq, const uint32_t* wus, const int32_t* offsets, int E_local, int H,
                             int I, int ldw, int M_cap, uint8_t* hq, uint32_t* hs, const MxSplit& sp,
-                            hipStream_t s) {
+                            hipStream_t s, int rows = 0) {
   GemmArgs g{};
   g.A = reinterpret_cast<const bf16_t*>(xq);
   g.B0 = reinterpret_cast<const bf16_t*>(wgq);
@@ -2288,11 +2323,8 @@ static hipError_t gateup_mx(const uint8_t* xq, const uint32_t* xs, const uint8_t
   g.Bs1 = wus;
   g.Cs = hs;
   const bool split = sp.plan != nullptr && H / kMxChunk >= 2 * kMinSplitChunks;
-  if (four_waves(true, M_cap, E_local, I))
-    grouped_gemm_mx_kernel<true, 4><<<mx_grid(M_cap, E_local, I, split || g.sk), 4 * kWave, 0, s>>>(g);
-  else
-    grouped_gemm_mx_kernel<true, 8><<<mx_grid(M_cap, E_local, I, split || g.sk), 8 * kWave, 0, s>>>(g);
-  hipError_t e = hipGetLastError();
+  hipError_t e = launch_waves(waves_for(true, M_cap, E_local, I, H, rows), g, mx_grid(M_cap, E_local, I, split || g.sk),
+                              s, grouped_gemm_mx_kernel<true, 4>, grouped_gemm_mx_kernel<true, 8>);
   if (e != hipSuccess || !split || sp.no_reduce) return e;
   split_reduce_mx_kernel<<<mx_reduce_grid(sp.plan_rows, I / 4), 256, 0, s>>>(sp.part, sp.plan, I, M_cap,
                                                                                      hq, hs);
@@ -2301,7 +2333,7 @@ static hipError_t gateup_mx(const uint8_t* xq, const uint32_t* xs, const uint8_t
 
 static hipError_t gemm_mx(const uint8_t* aq, const uint32_t* as, const uint8_t* bq, const uint32_t* bs,
                           const int32_t* offsets, int E_local, int N, int K, int ldb, int M_cap, void* c,
-                          const MxSplit& sp, hipStream_t s) {
+                          const MxSplit& sp, hipStream_t s, int rows = 0) {
   GemmArgs g{};
   g.A = reinterpret_cast<const bf16_t*>(aq);
   g.B0 = reinterpret_cast<const bf16_t*>(bq);
@@ -2316,11 +2348,9 @@ static hipError_t gemm_mx(const uint8_t* aq, const uint32_t* as, const uint8_t* 
   g.As = as;
   g.Bs0 = bs;
   const bool split = sp.plan != nullptr && K / kMxChunk >= 2 * kMinSplitChunks;
-  if (four_waves(false, M_cap, E_local, N))
-    grouped_gemm_mx_kernel<false, 4><<<mx_grid(M_cap, E_local, N, split || g.sk), 4 * kWave, 0, s>>>(g);
-  else
-    grouped_gemm_mx_kernel<false, 8><<<mx_grid(M_cap, E_local, N, split || g.sk), 8 * kWave, 0, s>>>(g);
-  hipError_t e = hipGetLastError();
+  hipError_t e = launch_waves(waves_for(false, M_cap, E_local, N, K, rows), g,
+                              mx_grid(M_cap, E_local, N, split || g.sk), s, grouped_gemm_mx_kernel<false, 4>,
+                              grouped_gemm_mx_kernel<false, 8>);
   if (e != hipSuccess || !split || sp.no_reduce) return e;
   split_reduce_kernel<false><<<mx_reduce_grid(sp.plan_rows, N / 4), 256, 0, s>>>(sp.part, sp.plan, N,
                                                                                   static_cast<bf16_t*>(c));
@@ -2344,7 +2374,7 @@ hipError_t launch_gemm_mx(const uint8_t* aq, const uint32_t* as, const uint8_t* 
 hipError_t launch_ffn_mx(const uint8_t* xq, const uint32_t* xs, const uint8_t* wgq, const uint32_t* wgs,
                          const uint8_t* wuq, const uint32_t* wus, const uint8_t* wdq, const uint32_t* wds,
                          const int32_t* offsets, int E_local, int H, int I, int ld_gu, int ld_dn, int M_cap,
-                         void* y_perm, void* ws, hipStream_t s) {
+                         void* y_perm, void* ws, hipStream_t s, int rows) {
   if (E_local == 0 || M_cap == 0) return hipSuccess;
   const FfnMxWs L = ffn_mx_ws_layout(M_cap, E_local, H, I);
   char* w = static_cast<char*>(ws);
@@ -2357,11 +2387,12 @@ hipError_t launch_ffn_mx(const uint8_t* xq, const uint32_t* xs, const uint8_t* w
   const bool no_reduce = M_cap <= kSkHostRows;
   const MxSplit sp1{reinterpret_cast<float*>(w + L.part), L.part_cap, reinterpret_cast<int32_t*>(w + L.plan),
                     L.plan_rows, cnt + kQueueGU, cnt + kDoneGU, cnt + kTcntGU, no_reduce, xcd_state(s)};
-  hipError_t e = gateup_mx(xq, xs, wgq, wgs, wuq, wus, offsets, E_local, H, I, ld_gu, M_cap, hq, hs, sp1, s);
+  hipError_t e = gateup_mx(xq, xs, wgq, wgs, wuq, wus, offsets, E_local, H, I, ld_gu, M_cap, hq, hs, sp1, s,
+                          rows);
   if (e != hipSuccess) return e;
   const MxSplit sp2{sp1.part, sp1.part_cap, sp1.plan, sp1.plan_rows, cnt + kQueueDN, cnt + kDoneDN, cnt + kTcntDN,
                     no_reduce, sp1.xcd};
-  return gemm_mx(hq, hs, wdq, wds, offsets, E_local, H, I, ld_dn, M_cap, y_perm, sp2, s);
+  return gemm_mx(hq, hs, wdq, wds, offsets, E_local, H, I, ld_dn, M_cap, y_perm, sp2, s, rows);
 }
 
 // ---------------------------------------------------------------------------

@@ -33,10 +33,12 @@ size_t ffn_ws_fixed(int M_cap, int E_local, int H, int I, bool bf16);
 // a_src != nullptr (bf16 only): the gate/up GEMM's row m is row
 // a_src[m] / a_div of x_perm, which then holds a_T rows (see GemmArgs).
 // ws_cap: bytes of ws when smaller than ffn_ws_bytes (>= ffn_ws_fixed).
+// rows: rows an expert is expected to have, 0 if the caller cannot say; chooses
+// between kernels of equal results (see waves_for).
 hipError_t launch_ffn(const void* x_perm, const void* w_gate, const void* w_up, const void* w_down,
                       const int32_t* offsets, int E_local, int H, int I, int ld_gu, int ld_dn, int M_cap, bool bf16,
                       void* y_perm, void* ws, hipStream_t s, const int32_t* a_src = nullptr, int a_div = 1,
-                      int a_T = 0, size_t ws_cap = SIZE_MAX);
+                      int a_T = 0, size_t ws_cap = SIZE_MAX, int rows = 0);
 // The FFN scratch of this process on the current device (kScratchBytes),
 // resolved on first use; its counters are cleared on stream s then.
 constexpr size_t kScratchBytes = (size_t)128 << 20;
@@ -57,7 +59,7 @@ size_t ffn_mx_ws_bytes(int M_cap, int E_local, int H, int I);
 hipError_t launch_ffn_mx(const uint8_t* xq, const uint32_t* xs, const uint8_t* wgq, const uint32_t* wgs,
                          const uint8_t* wuq, const uint32_t* wus, const uint8_t* wdq, const uint32_t* wds,
                          const int32_t* offsets, int E_local, int H, int I, int ld_gu, int ld_dn, int M_cap,
-                         void* y_perm, void* ws, hipStream_t s);
+                         void* y_perm, void* ws, hipStream_t s, int rows = 0);
 
 // compute units of the current device (256 if it cannot be asked)
 int device_cu_count();

@@ -299,7 +299,17 @@ moe_status moe_grouped_swiglu_ffn_gather(const void* x, const int32_t* perm_src,
                                          const void* w_up, const void* w_down, const int32_t* offsets, int E_local,
                                          int H, int I, int ldw_gu, int ldw_dn, int M_cap, moe_dtype dt,
                                          void* y_perm, void* ws, size_t* ws_bytes, hipStream_t stream) {
+  return moe_grouped_swiglu_ffn_gather_of(x, perm_src, T, k, w_gate, w_up, w_down, offsets, 0, E_local, H, I, ldw_gu,
+                                          ldw_dn, M_cap, dt, y_perm, ws, ws_bytes, stream);
+}
+
+moe_status moe_grouped_swiglu_ffn_gather_of(const void* x, const int32_t* perm_src, int T, int k, const void* w_gate,
+                                            const void* w_up, const void* w_down, const int32_t* offsets, int E,
+                                            int E_local, int H, int I, int ldw_gu, int ldw_dn, int M_cap,
+                                            moe_dtype dt, void* y_perm, void* ws, size_t* ws_bytes,
+                                            hipStream_t stream) {
   moe_status st = ffn_shape_ok(E_local, H, I, M_cap, dt);
+  if (st == MOE_OK && E != 0 && (E < E_local || E > MOE_MAX_EXPERTS)) st = MOE_ERR_INVALID_ARG;
   if (st != MOE_OK) return st;
   int ld_gu = 0, ld_dn = 0;
   if ((st = resolve_ld(ldw_gu, H, dt, &ld_gu)) != MOE_OK || (st = resolve_ld(ldw_dn, I, dt, &ld_dn)) != MOE_OK)
@@ -320,7 +330,8 @@ moe_status moe_grouped_swiglu_ffn_gather(const void* x, const int32_t* perm_src,
       !aligned16(ws) || !aligned4(offsets) || !aligned4(perm_src))
     return MOE_ERR_INVALID_ARG;
   return hip_status(moe::launch_ffn(x, w_gate, w_up, w_down, offsets, E_local, H, I, ld_gu, ld_dn, M_cap, true,
-                                    y_perm, ws, stream, perm_src, k, T));
+                                    y_perm, ws, stream, perm_src, k, T, SIZE_MAX,
+                                    E == 0 ? 0 : (int)std::max(1LL, (long long)T * k / E)));
 }
 
 moe_status moe_unpermute_combine(const void* y_perm, const float* topk_w, const int32_t* dest, int T, int k,

@@ -388,3 +388,18 @@ def test_mx_weight_row_strides(L):
                                None, None, ctypes.byref(n), None, None, None) == 0
     assert L.moe_load_sweep_mx(*([FAKE] * 8), 1, 4096, 14336, 4104, 0, Ms.ctypes.data_as(ctypes.c_void_p), 2, 1, 3,
                                None, None, ctypes.byref(n), None, None, None) == INVALID
+
+
+def test_ffn_gather_of_checks_the_layer(L):
+    """E = 0 (not known) or E_local <= E <= 256; the rest as the gather call's."""
+    n = ctypes.c_size_t(0)
+    for E in (-1, 7, 257):
+        assert L.moe_grouped_swiglu_ffn_gather_of(None, None, 64, 2, None, None, None, None, E, 8, 128, 128, 0, 0, 128,
+                                                  1, None, None, ctypes.byref(n), None) == _lib.MOE_ERR_INVALID_ARG
+    want = ctypes.c_size_t(0)
+    assert L.moe_grouped_swiglu_ffn_gather(None, None, 64, 2, None, None, None, None, 8, 128, 128, 0, 0, 128, 1, None,
+                                           None, ctypes.byref(want), None) == _lib.MOE_OK
+    for E in (0, 8, 256):
+        assert L.moe_grouped_swiglu_ffn_gather_of(None, None, 64, 2, None, None, None, None, E, 8, 128, 128, 0, 0, 128,
+                                                  1, None, None, ctypes.byref(n), None) == _lib.MOE_OK
+        assert n.value == want.value
