@@ -384,7 +384,8 @@ moe_status moe_load_sweep(const void* x, const void* w_gate, const void* w_up, c
     const char* g = static_cast<const char*>(w_gate) + (size_t)rot * wgu;
     const char* u = static_cast<const char*>(w_up) + (size_t)rot * wgu;
     const char* d = static_cast<const char*>(w_down) + (size_t)rot * wdn;
-    return moe::launch_ffn(x, g, u, d, offsets, 1, H, I, ld_gu, ld_dn, m, bf16, y_scratch, ws, stream);
+    return moe::launch_ffn(x, g, u, d, offsets, 1, H, I, ld_gu, ld_dn, m, bf16, y_scratch, ws, stream, nullptr, 1, 0,
+                           SIZE_MAX, m);
   });
 }
 
@@ -426,7 +427,7 @@ moe_status moe_load_sweep_mx(const uint8_t* xq, const uint32_t* xs, const uint8_
   return sweep_loop(Ms, nM, warmup, iters, n_rot, offsets, us_out, us_all, stream, [&](int rot, int m) {
     return moe::launch_ffn_mx(xq, xs, wgq + rot * wgu, wgs + rot * smat, wuq + rot * wgu, wus + rot * smat,
                               wdq + rot * wdn, wds + rot * sdown, offsets, 1, H, I, ld_gu, ld_dn, max_m, y_scratch,
-                              ws, stream);
+                              ws, stream, m);
   });
 }
 
