@@ -190,9 +190,7 @@ __device__ __forceinline__ void split_epilogue(const f32x16_t (&acc)[NB][MI][NI]
                             acc[b][i][j][4 * g + 3]);
         __builtin_amdgcn_sched_barrier(0);
         float* out = pbase + b * pstride + (size_t)r0 * ld + col0 + wn * WN;
-#pragma unroll
-        for (int it = 0; it < 32 * PP / 64; ++it) {
-          if (m0 + r0 + it * (64 / PP) >= m_end) break;  // a decode tile has a row or a few
+        auto store = [&](int it) {
           const int row = (it * 64 + lane) / PP, p = lane % PP;
           const f32x4_t v = *reinterpret_cast<const f32x4_t*>(blk + row * RB + ((p ^ key(row)) * 16));
           if (m0 + r0 + row < m_end) {
@@ -202,6 +200,11 @@ __device__ __forceinline__ void split_epilogue(const f32x16_t (&acc)[NB][MI][NI]
             else
               *reinterpret_cast<f32x4_t*>(q) = v;
           }
+        };
+        store(0);
+        if (m0 + r0 + 64 / PP < m_end) {  // a decode tile has a row or a few
+#pragma unroll
+          for (int it = 1; it < 32 * PP / 64; ++it) store(it);
         }
         __builtin_amdgcn_sched_barrier(0);
       }
