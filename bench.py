@@ -163,7 +163,7 @@ def main():
             ev[3].record()
             if fuse:
                 yp, _ = moe.moe_grouped_swiglu_ffn_gather(xb, ps, k, wg, wu, wd, offsets, ws=bb["ffn_ws"],
-                                                          y_perm=bb["y_perm"])
+                                                          y_perm=bb["y_perm"], experts=E)
             else:
                 yp, _ = moe.moe_grouped_swiglu_ffn(xp, wg, wu, wd, offsets, ws=bb["ffn_ws"], y_perm=bb["y_perm"])
             ev[4].record()
@@ -313,7 +313,7 @@ def time_layer(moe, torch, np, x, wr, bias, k, emap, wg, wu, wd, bb, steps, warm
         ev[3].record()
         if fuse:
             yp, _ = moe.moe_grouped_swiglu_ffn_gather(x, ps, k, wg, wu, wd, offsets, ws=bb["ffn_ws"],
-                                                      y_perm=bb["y_perm"])
+                                                      y_perm=bb["y_perm"], experts=E)
         else:
             yp, _ = moe.moe_grouped_swiglu_ffn(xp, wg, wu, wd, offsets, ws=bb["ffn_ws"], y_perm=bb["y_perm"])
         ev[4].record()

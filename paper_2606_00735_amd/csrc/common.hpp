@@ -106,7 +106,10 @@ __device__ __forceinline__ const void* uniform_ptr(const void* p) {
   return reinterpret_cast<const void*>((static_cast<uint64_t>(hi) << 32) | lo);
 }
 
-// dma16s / dma4s to an LDS byte address (wave-uniform).
+// dma16s / dma4s to an LDS byte address (wave-uniform). The waits before the
+// load: the compiler does not see that the asm reads sbase in a vector memory
+// instruction, five wait states after a vector instruction may have written it
+// (s_mov and s_nop 3), and M0 needs one.
 __device__ __forceinline__ void dma16a(const void* sbase, uint32_t voff, uint32_t m0) {
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %0, %1"
                :
@@ -250,10 +253,12 @@ __device__ __forceinline__ void pipeline(int nK, bf16_t* smem, int stage_elems, 
 // refill an operand register right after its last MFMA of the k-step instead
 // of keeping a second buffer for it.
 //
-// The loads of a chunk leave in KS parts, issue(kc, live, stage, part), one
+// The loads of a chunk may leave in KS parts, issue(kc, live, stage, part), one
 // per k-step from the one after the barrier on: a burst of all of them fills
 // the CU's miss queue, and the wave then sits in the issue of the rest while
-// its MFMAs wait behind them. part < 0 asks for all parts at once (prologue).
+// its MFMAs wait behind them. part < 0 asks for all parts at once (prologue). A
+// consumer whose loads all leave in part 0 (the router, two-stage tiles, MXFP8
+// on 8 waves) does nothing for the others.
 template <int NS, int LOADS, int KS, bool MMA_FIRST = false, class Issue, class Read, class Mma, class Mix>
 __device__ __forceinline__ void pipeline_xk(int nK, bf16_t* smem, int stage_elems, Issue&& issue, Read&& read,
                                             Mma&& mma, Mix&& mix) {

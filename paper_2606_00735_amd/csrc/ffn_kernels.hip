@@ -35,9 +35,10 @@ constexpr int kBK = 64;  // K chunk per pipeline stage (128-byte tile rows)
 // (Stages below).
 //
 // Blocks have W waves. W = 4, one wave per SIMD with the whole register file,
-// is what the large tile needs. W = 8 serves launches in which no expert can
-// have more than 128 rows: the small and mid tiles run 2-7 % faster with a
-// second wave per SIMD covering the first one's LDS waits and epilogue.
+// is what the large tile in quadrant phases needs. With W = 8 the small and mid
+// tiles run 2-7 % faster (more where few rows are there), a second wave per SIMD
+// covering the first one's LDS waits and epilogue. waves_for chooses; either
+// kernel has every class.
 constexpr int kMaxWaves = 8;
 constexpr int kSmallM = 64;
 
@@ -134,10 +135,6 @@ __device__ __forceinline__ float silu_mul_fast(float g, float u) {
   return (g * sig) * u;
 }
 
-// Split-K epilogue shared by the bf16 and MXFP8 tiles: the fp32 sums of
-// output (r, c) of matrix b (r, c within the tile) go to
-// pbase[b * pstride + r * ld + col0 + c]; each lane writes its 4 consecutive
-// columns per group as one 16-byte store.
 // 16-byte stores and loads at agent scope, as two 64-bit relaxed atomic
 // accesses (gfx950 gives them the sc1 cache policy): the store writes through
 // to the device's point of coherence and the load reads from it, so a block
@@ -159,12 +156,15 @@ __device__ __forceinline__ f32x4_t ld_coh4(const float* p) {
                  __uint_as_float((uint32_t)hi), __uint_as_float((uint32_t)(hi >> 32))};
 }
 
+// Split-K epilogue shared by the bf16 and MXFP8 tiles: the fp32 sums of
+// output (r, c) of matrix b (r, c within the tile) go to
+// pbase[b * pstride + r * ld + col0 + c], through LDS as in store_block (32
+// rows of one matrix at a time: a direct store touches 32 rows with 32 bytes
+// each).
 // COH: the sums are for another block to read in the same launch (see
 // decode_schedule) and the stores have completed on return; coh: stored with
 // st_coh4, for a block on another XCD, else with ordinary stores, which a
 // block on the same XCD reads from their shared L2.
-// Through LDS as in store_block (32 rows of one matrix at a time: a direct
-// store touches 32 rows with 32 bytes each).
 template <int MI, int NI, int NB, int WM, int WN, bool COH = false>
 __device__ __forceinline__ void split_epilogue(const f32x16_t (&acc)[NB][MI][NI], bf16_t* smem, int m0, int m_end,
                                                int col0, int ld, int wm, int wn, int wave, int lane, float* pbase,
@@ -332,6 +332,9 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, bf16_t* smem, int e
   if (kc1 < 0) kc1 = K / kBK;
   // part: the share of the chunk's loads to issue (pipeline_xk); < 0: all.
   // With two stages all leave at once: the last would have no time to land.
+  // 8 waves, FFN us, all at once / in parts: one row, Qwen3-shaped 20.0 / 19.5,
+  // DSV3-shaped 35.6 / 34.7; Mixtral-shaped T = 32 481.2 / 480.0, Qwen3-shaped
+  // T = 128 220.7 / 219.3; one Maverick-shaped expert of 300 rows 195.4 / 186.5.
   constexpr int KS = kBK / 16;
   auto issue = [&](int kc, bool live, bf16_t* st, int part) {
     const int msk = live ? -1 : 0;
@@ -391,8 +394,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, bf16_t* smem, int e
   // Epilogue. The MFMAs computed transposed 32x32 blocks (weights as the A
   // operand): register v of lane l holds output column 8 * (v / 4) +
   // 4 * (l / 32) + (v % 4) of the block for row (token) l % 32, so each lane
-  // owns 4 consecutive columns per group g = v / 4 and stores them as one
-  // 8-byte write (or, for a split-K partial, one 16-byte fp32 write).
+  // owns 4 consecutive columns per group g = v / 4, which store_block (or, for
+  // a split-K partial, split_epilogue) regroups into whole rows.
   if (SPLIT) {
     split_epilogue<MI, NI, NB, WM, WN, COH>(acc, smem, m0, m_end, pcol0, pld, wm, wn, wave, lane, pbase, pstride,
                                             coh);
@@ -410,9 +413,9 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, bf16_t* smem, int e
 }
 
 // MXFP8 stages: the same 128-byte tile rows as the bf16 path (a K chunk is
-// 128 E4M3 codes), plus one scale dword per operand row. Every wave loads 64
-// scale rows per chunk (one global_load_lds_dword), so a stage holds
-// W * 64 = 512 scale rows whatever its operand rows.
+// 128 E4M3 codes), plus one scale dword per operand row. A
+// global_load_lds_dword of a wave brings 64 scale rows, so a stage has room for
+// SLOADS * W * 64 of them, a multiple of what all waves load at once.
 template <int BM, int BN, bool DUAL, int W>
 struct MxStages {
   static constexpr int NB = DUAL ? 2 : 1;
@@ -681,12 +684,14 @@ __device__ __forceinline__ void gemm_tile_mx(const GemmArgs& a, bf16_t* smem, in
 // for eight 64 x 128 ones.
 //
 // What bounds it is the chip's power: one 8192 x 28672 x 4096 product of
-// normally distributed values runs at 1290 TFLOP/s with the clock pulled down
-// to 1.58 GHz (77 % of the MFMA rate at that clock; all-zero operands, 1886
-// TFLOP/s at 2.37 GHz), its MFMAs alone at 1640 TFLOP/s and 1.97 GHz, MFMAs
-// and LDS reads at 1530. Against the 8-wave tile, same box: gate/up of the
-// Mixtral-shaped T = 4096 batch 1723 -> 1633 us, DSV3-shaped shard 986 -> 898,
-// Maverick-shaped 903 -> 815, MXFP8 Mixtral-shaped 916 -> 870 us.
+// normally distributed values (gate/up of 8192 rows) runs at 1306 TFLOP/s with
+// the clock at 1.74 GHz and the MFMA pipes busy 69 % of it, the same product of
+// zeros at 1714 TFLOP/s, 2.32 GHz and the same 70 % (MXFP8 2404 and 2876).
+// Against the 8-wave tile, same box: gate/up of the Mixtral-shaped T = 4096
+// batch 1723 -> 1633 us, DSV3-shaped shard 986 -> 898, Maverick-shaped 903 ->
+// 815, MXFP8 Mixtral-shaped 916 -> 870 us.
+// The K loop holds everything in registers; around it, once a tile, 54 to 68
+// VGPRs go to scratch and back (216 to 276 bytes a lane).
 // ---------------------------------------------------------------------------
 constexpr int kSlotRows = 128;
 constexpr int kSlotElems = kSlotRows * kBK;  // bf16 elements: 16 KB
