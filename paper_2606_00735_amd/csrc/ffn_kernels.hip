@@ -165,10 +165,35 @@ __device__ __forceinline__ f32x4_t ld_coh4(const float* p) {
 // decode_schedule) and the stores have completed on return; coh: stored with
 // st_coh4, for a block on another XCD, else with ordinary stores, which a
 // block on the same XCD reads from their shared L2.
-template <int MI, int NI, int NB, int WM, int WN, bool COH = false>
+// DIRECT: tiles of at most that many rows are stored from the registers: where
+// they leave most waves without rows, one wave's turn through LDS is a chain of
+// its own (the router's 256-row tile, us, E = 256, H = 7168, direct / LDS: 64
+// tokens 33.3 / 34.6, 16 tokens 32.0 / 32.8; 200 tokens 37.6 / 36.0).
+template <int MI, int NI, int NB, int WM, int WN, bool COH = false, int DIRECT = 0>
 __device__ __forceinline__ void split_epilogue(const f32x16_t (&acc)[NB][MI][NI], bf16_t* smem, int m0, int m_end,
                                                int col0, int ld, int wm, int wn, int wave, int lane, float* pbase,
                                                size_t pstride, bool coh) {
+  if constexpr (DIRECT > 0 && !COH) {
+    if (m_end - m0 <= DIRECT) {
+#pragma unroll
+      for (int i = 0; i < MI; ++i) {
+        const int r = wm * WM + i * 32 + (lane & 31);
+        if (m0 + r < m_end) {
+          float* p = pbase + (size_t)r * ld + col0 + wn * WN + 4 * (lane >> 5);
+#pragma unroll
+          for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int j = 0; j < NI; ++j)
+#pragma unroll
+              for (int g = 0; g < 4; ++g)
+                *reinterpret_cast<f32x4_t*>(p + b * pstride + j * 32 + 8 * g) =
+                    f32x4_t{acc[b][i][j][4 * g], acc[b][i][j][4 * g + 1], acc[b][i][j][4 * g + 2],
+                            acc[b][i][j][4 * g + 3]};
+        }
+      }
+      return;
+    }
+  }
   constexpr int RB = WN * 4, PP = RB / 16;  // bytes and 16-byte pieces of a row
   static_assert(RB == 512 || RB == 256 || RB == 128, "row bytes");
   auto key = [](int r) { return PP >= 16 ? (r & 15) : ((r >> 1) & 7); };  // see store_block
@@ -276,7 +301,7 @@ __device__ __forceinline__ void store_block(bf16_t* smem, void* C, int N, int ro
 // SPLIT: only K chunks [kc0, kc1) are summed and the fp32 sums of output
 // (r, c) (r: row within the tile, c: column within the tile) go to
 // pbase[b * pstride + r * pld + pcol0 + c] instead of C.
-template <int W, int BM, int BN, int WAVES_M, bool DUAL, bool SPLIT = false, bool COH = false>
+template <int W, int BM, int BN, int WAVES_M, bool DUAL, bool SPLIT = false, bool COH = false, int DIRECT = 0>
 __device__ __forceinline__ void gemm_tile(const GemmArgs& a, bf16_t* smem, int e, int m0, int m_end, int n0,
                                           int kc0 = 0, int kc1 = -1, float* pbase = nullptr,
                                           size_t pstride = 0, int pld = 0, int pcol0 = 0, bool coh = true) {
@@ -397,7 +422,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, bf16_t* smem, int e
   // owns 4 consecutive columns per group g = v / 4, which store_block (or, for
   // a split-K partial, split_epilogue) regroups into whole rows.
   if (SPLIT) {
-    split_epilogue<MI, NI, NB, WM, WN, COH>(acc, smem, m0, m_end, pcol0, pld, wm, wn, wave, lane, pbase, pstride,
+    split_epilogue<MI, NI, NB, WM, WN, COH, DIRECT>(acc, smem, m0, m_end, pcol0, pld, wm, wn, wave, lane, pbase, pstride,
                                             coh);
     return;
   }
@@ -2421,7 +2446,7 @@ __global__ __launch_bounds__(512) void router_logits_split_kernel(GemmArgs a, in
   const int nK = a.K / kBK, sp = (int)blockIdx.y;
   const int kc0 = sp * nK / S, kc1 = (sp + 1) * nK / S;
   float* pbase = part + ((size_t)sp * T + m0) * BN;
-  gemm_tile<8, 256, BN, 4, false, true>(a, smem, 0, m0, m_end, 0, kc0, kc1, pbase, 0, BN, 0);
+  gemm_tile<8, 256, BN, 4, false, true, false, 64>(a, smem, 0, m0, m_end, 0, kc0, kc1, pbase, 0, BN, 0);
 }
 
 hipError_t launch_router_logits_split(const void* x, const void* wr, int T, int H, int E, int S, float* part,
