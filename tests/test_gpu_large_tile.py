@@ -147,3 +147,39 @@ def test_mx(H, I, rows):
         ref = hv[r] @ d.t()
         dy = I * 2.0 ** -23 * (hv[r].abs() @ d.abs().t())
         assert bool(((y[r].double() - ref).abs() <= 2.0 ** -8 * ref.abs() + dy).all()), f"y {e}"
+
+
+@pytest.mark.parametrize("layer", [0, 1])
+def test_captured(layer):
+    """Both kernels launched and the offsets choosing (layer unknown), or 4 waves:
+    replays of a graph give the eager bits, with other rows in between."""
+    H, I, rows = 4224, 512, [1100]
+    x, wg, wu, wd, off = _inputs(H, I, rows, 5)
+    M = x.shape[0]
+    src = torch.arange(M, dtype=torch.int32, device="cuda")
+    ws = torch.zeros(moe.ffn_ws_bytes(1, H, I, M, x.dtype), dtype=torch.uint8, device="cuda")
+    y = torch.empty_like(x)
+
+    def call():
+        moe.moe_grouped_swiglu_ffn_gather(x, src, 1, wg, wu, wd, off, ws=ws, y_perm=y, experts=layer)
+
+    call()
+    torch.cuda.synchronize()
+    few = off.clone()
+    few[1] = 40  # a launch for the 8-wave kernel where the offsets choose
+    full, want = off.clone(), []
+    for o in (full, few):
+        off.copy_(o)
+        y.fill_(float("nan"))
+        call()
+        want.append(y.clone())
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call()
+    for i in (0, 1, 0, 1):
+        off.copy_((full, few)[i])
+        y.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y.view(torch.int16), want[i].view(torch.int16)), i
